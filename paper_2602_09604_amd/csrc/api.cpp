@@ -11,6 +11,7 @@
 #include <unordered_map>
 
 #include "sv_internal.h"
+#include "sweep.h"
 
 struct sv_state {
   int n = 0;
@@ -38,7 +39,7 @@ struct sv_state {
   // the call that produced the kept graph (gates, options, planning epoch)
   // and its pass figures: an identical call relaunches without fusing again
   std::vector<unsigned char> graph_input;
-  uint64_t graph_passes = 0, graph_bytes = 0;
+  uint64_t graph_passes = 0, graph_launches = 0, graph_bytes = 0;
   double graph_flops = 0.0;
   bool graph_launched = false;  // the last run_passes launched the kept graph
   hipStream_t capture_stream = nullptr;  // graphs are captured here, launched on `stream`
@@ -156,16 +157,25 @@ static void drop_graph(sv_state* s) {
   }
 }
 
+// What a call launches: one pass, or several as one tile sweep (T > 0).
+struct Launch {
+  Sweep sweep;
+  size_t off = 0, bytes = 0;  // its data, from the start of the call's data
+};
+
 // Everything a captured graph depends on besides the state buffer: each
-// pass's launch parameters and the encoded pass data (offsets relative to the
+// launch's parameters and the encoded pass data (offsets relative to the
 // start of the data).
-static std::vector<unsigned char> graph_key(const std::vector<Pass>& passes, const unsigned char* data,
-                                            size_t total) {
+static std::vector<unsigned char> graph_key(const std::vector<Launch>& launches, const std::vector<Pass>& passes,
+                                            const unsigned char* data, size_t total) {
   std::vector<int64_t> f;
-  f.reserve(passes.size() * 28);
-  for (const Pass& p : passes) {
-    f.insert(f.end(), {p.k, p.variant, p.precision, (int64_t)p.mat_off, (int64_t)p.mat_bytes, p.tile_bits,
-                       p.reg_iters, p.mfma_cols, (int64_t)p.cmask, (int64_t)p.cval, p.nmux, p.mfma_x});
+  f.reserve(launches.size() * 22);
+  for (const Launch& l : launches) {
+    f.insert(f.end(), {l.sweep.T, (int64_t)l.sweep.bits, (int64_t)l.sweep.mat_bytes, (int64_t)l.off, (int64_t)l.bytes});
+    if (l.sweep.T) continue;  // a sweep's passes are in its data
+    const Pass& p = passes[l.sweep.members[0]];
+    f.insert(f.end(), {p.k, p.variant, p.precision, p.tile_bits, p.reg_iters, p.mfma_cols, (int64_t)p.cmask,
+                       (int64_t)p.cval, p.nmux, p.mfma_x});
     f.insert(f.end(), p.s, p.s + SV_MAX_K);
   }
   std::vector<unsigned char> key(f.size() * sizeof(int64_t) + total);
@@ -194,14 +204,11 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
   std::vector<const double*> mats;               // matrix passes: the fused matrix
   std::vector<std::vector<const double*>> mux;   // multiplexed passes: the matrix of each control value
   std::vector<std::vector<unsigned char>> phase_bytes;  // phase passes: their coefficients and table
-  size_t total = 0;
   auto add = [&](Pass& p) {
     if (p.variant == V_MFMA) {
       p.mfma_x = mfma_exchange_mask(s->n, p);
       p.mat_bytes = pass_data_bytes(p);
     }
-    p.mat_off = total;
-    total += align256(p.mat_bytes);
     passes.push_back(p);
   };
   for (size_t i = 0; i < fused.size();) {
@@ -290,23 +297,67 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
     phase_bytes.emplace_back();
     ++i;
   }
-  if (total == 0) return;
-  const size_t base = arena_take(s, total);
-  std::vector<size_t> rel(passes.size());  // offsets of each pass's data from base
-  for (size_t i = 0; i < passes.size(); ++i) rel[i] = passes[i].mat_off;
-  auto encode = [&](size_t i) {
-    unsigned char* dst = s->arena_host + base + rel[i];
-    if (passes[i].variant == V_PHASE) {
-      std::memcpy(dst, phase_bytes[i].data(), passes[i].mat_bytes);
-    } else if (passes[i].nmux > 1) {
-      const size_t each = passes[i].mat_bytes / passes[i].nmux;
-      for (int v = 0; v < passes[i].nmux; ++v) encode_pass_data(passes[i], mux[i][v], dst + v * each);
-    } else {
-      encode_pass_data(passes[i], mats[i], dst);
-    }
-  };
+  if (passes.empty()) return;
   const bool timing = o.timing && stats;
   const bool graph = o.use_graph && !timing;
+  // Consecutive passes that fit in one tile go out as one sweep; a timed call
+  // and one with a forced variant launch every pass by itself.
+  std::vector<Launch> launches;
+  {
+    const bool sweeps = !timing && o.variant == SV_VARIANT_AUTO && s->n >= kSweepMinBits;
+    std::vector<SweepItem> items(passes.size());
+    for (size_t i = 0; i < passes.size(); ++i) {
+      const Pass& p = passes[i];
+      items[i].mask = p.cmask;
+      for (int j = 0; j < p.k; ++j) items[i].mask |= (uint64_t)1 << p.s[j];
+      if (p.variant == V_PHASE) items[i].mask = ~(uint64_t)0;
+      if (sweeps && p.variant != V_PHASE && !p.cmask) items[i].kind = sweep_kind(s->n, p.k, p.precision);
+    }
+    std::vector<Sweep> plan;
+    plan_sweeps(items, s->n, plan);
+    launches.resize(plan.size());
+    for (size_t i = 0; i < plan.size(); ++i) launches[i].sweep = std::move(plan[i]);
+  }
+  size_t total = 0;
+  for (Launch& l : launches) {
+    if (l.sweep.T && (l.sweep.members.size() > 1 || passes[l.sweep.members[0]].k >= 5)) {
+      l.bytes = l.sweep.data_bytes;
+    } else {
+      l.sweep.T = 0;
+      l.bytes = passes[l.sweep.members[0]].mat_bytes;
+    }
+    l.off = total;
+    total += align256(l.bytes);
+  }
+  const size_t base = arena_take(s, total);
+  auto encode = [&](size_t i) {
+    const Launch& l = launches[i];
+    unsigned char* dst = s->arena_host + base + l.off;
+    if (l.sweep.T) {
+      std::vector<const Pass*> ps;
+      std::vector<const double*> ms;
+      for (int m : l.sweep.members) {
+        ps.push_back(&passes[m]);
+        ms.push_back(mats[m]);
+      }
+      encode_sweep(l.sweep, ps, ms, dst);
+      return;
+    }
+    const int m = l.sweep.members[0];
+    const Pass& p = passes[m];
+    if (p.variant == V_PHASE) {
+      std::memcpy(dst, phase_bytes[m].data(), p.mat_bytes);
+    } else if (p.nmux > 1) {
+      const size_t each = p.mat_bytes / p.nmux;
+      for (int v = 0; v < p.nmux; ++v) encode_pass_data(p, mux[m][v], dst + v * each);
+    } else {
+      encode_pass_data(p, mats[m], dst);
+    }
+  };
+  auto send = [&](const Launch& l, const unsigned char* data, hipStream_t st) {
+    if (l.sweep.T) launch_sweep(l.sweep, s->n, s->psi, data + l.off, st);
+    else launch_pass(passes[l.sweep.members[0]], s->n, s->psi, data + l.off, st);
+  };
   if (timing)
     while (s->pass_events.size() < 2 * passes.size()) {  // a start and an end per pass
       hipEvent_t e;
@@ -315,14 +366,14 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
     }
   auto launch = [&](size_t i) {
     if (timing) SV_HIP(hipEventRecord(s->pass_events[2 * i], s->stream));
-    launch_pass(passes[i], s->n, s->psi, s->arena_dev, s->stream);
+    send(launches[i], s->arena_dev + base, s->stream);
     if (timing) SV_HIP(hipEventRecord(s->pass_events[2 * i + 1], s->stream));
   };
   if (graph) {
-    for (size_t i = 0; i < passes.size(); ++i) encode(i);
+    for (size_t i = 0; i < launches.size(); ++i) encode(i);
     // The graph reads its pass data from its own buffer, so ring uploads of
     // later calls never disturb it; relaunch when nothing it encodes changed.
-    std::vector<unsigned char> key = graph_key(passes, s->arena_host + base, total);
+    std::vector<unsigned char> key = graph_key(launches, passes, s->arena_host + base, total);
     const bool relaunch = s->graph_exec && key == s->graph_key;
     if (stats) stats->graph_relaunched = relaunch ? 1 : 0;
     if (!relaunch) {
@@ -342,7 +393,7 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
       hipStream_t cs = s->capture_stream;
       SV_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
       try {
-        for (const Pass& p : passes) launch_pass(p, s->n, s->psi, s->graph_dev, cs);
+        for (const Launch& l : launches) send(l, s->graph_dev, cs);
       } catch (...) {
         hipGraph_t g = nullptr;
         (void)hipStreamEndCapture(cs, &g);
@@ -361,6 +412,7 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
     }
     s->graph_launched = true;
     s->graph_passes = passes.size();
+    s->graph_launches = launches.size();
     s->graph_bytes = 0;
     s->graph_flops = 0.0;
     for (const Pass& p : passes) {
@@ -370,22 +422,21 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
     if (stats) SV_HIP(hipEventRecord(s->ev0, s->stream));
     SV_HIP(hipGraphLaunch(s->graph_exec, s->stream));
   } else {
-    // Passes go out in chunks: the first pass alone, then each time as many
+    // Launches go out in chunks: the first alone, then each time as many
     // as the host encodes while the GPU still has queued work (an event after
     // every chunk tells), so encoding hides behind the passes instead of
     // preceding them.
-    for (Pass& p : passes) p.mat_off += base;
     size_t next = 0;
-    while (next < passes.size()) {
+    while (next < launches.size()) {
       const size_t lo = next;
       encode(next++);
-      while (lo > 0 && next < passes.size()) {
+      while (lo > 0 && next < launches.size()) {
         const hipError_t q = hipEventQuery(s->queued);
         if (q == hipSuccess) break;  // the GPU ran dry: send what is ready
         if (q != hipErrorNotReady) throw DeviceError{q, "hipEventQuery"};
         encode(next++);
       }
-      const size_t from = rel[lo], to = next < passes.size() ? rel[next] : total;
+      const size_t from = launches[lo].off, to = next < launches.size() ? launches[next].off : total;
       SV_HIP(hipMemcpyAsync(s->arena_dev + base + from, s->arena_host + base + from, to - from,
                             hipMemcpyHostToDevice, s->stream));
       if (lo == 0 && stats) SV_HIP(hipEventRecord(s->ev0, s->stream));
@@ -400,7 +451,7 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
     SV_HIP(hipEventElapsedTime(&ms, s->ev0, s->ev1));
     stats->gpu_s = ms * 1e-3;
     stats->passes = passes.size();
-    stats->launches = passes.size();
+    stats->launches = launches.size();
     stats->bytes = 0;
     double fl = 0.0;
     for (const Pass& p : passes) {
@@ -717,7 +768,7 @@ int sv_apply_circuit(sv_state* s, const sv_gate* gates, size_t n_gates, const sv
         SV_HIP(hipEventElapsedTime(&ms, s->ev0, s->ev1));
         stats->gpu_s = ms * 1e-3;
         stats->passes = s->graph_passes;
-        stats->launches = s->graph_passes;
+        stats->launches = s->graph_launches;
         stats->bytes = s->graph_bytes;
         stats->useful_flops = s->graph_flops;
         stats->gates_in = n_gates;

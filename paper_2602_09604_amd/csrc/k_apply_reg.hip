@@ -242,8 +242,7 @@ void launch_lds(const Pass& p, int n, void* psi, const float2* U, hipStream_t st
 
 // Host checks of the launch geometry happen in the planner (targets sorted,
 // distinct, < n; k <= n; LDS tile fits); this only dispatches.
-void launch_pass(const Pass& p, int n, void* psi, const unsigned char* arena_dev, hipStream_t st) {
-  const unsigned char* data = arena_dev + p.mat_off;
+void launch_pass(const Pass& p, int n, void* psi, const unsigned char* data, hipStream_t st) {
   if (p.variant == V_MFMA) {  // with or without controls
     launch_mfma(p, n, psi, data, st);
   } else if (p.cmask) {

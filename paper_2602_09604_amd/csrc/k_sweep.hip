@@ -1,0 +1,318 @@
+// Tile sweeps: several gate passes in one read and write of the state (see
+// sweep.h for the scheme).
+//
+// Every pass of a sweep runs on the tile in LDS, so a sweep of m passes moves
+// 16 bytes per amplitude through HBM once instead of m times.  A k = 3..6
+// pass is a real GEMM in the 4M form ([Yr; Yi] = [[Ur, -Ui], [Ui, Ur]] [Xr; Xi]) on
+// v_mfma_f32_16x16x4_f32: FP32 products and FP32 accumulation.  Lane (h, j)
+// of a unit (16 groups of 2^K amplitudes) holds the amplitudes h 2^(K-2) + i of
+// group j: the rows and columns of the real matrix are ordered on the host so
+// that a lane's inputs and its outputs are the same amplitudes, and a pass
+// reads and writes its tile in place with no exchange between lanes.  k = 1, 2
+// passes multiply on the vector ALUs, each lane on four amplitudes of its own.
+#include "k_common.h"
+#include "sweep.h"
+
+namespace sv {
+
+namespace {
+using namespace kern;
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Slots are float4 (two amplitudes); slot bits 0..3 are XORed with bits 4..7
+// and 8..11 so that strided accesses spread over the LDS banks.
+__device__ __forceinline__ int swz(int e) { return e ^ (((e >> 4) ^ (e >> 8)) & 15); }
+
+// Barrier between the passes on a tile: orders the LDS accesses of the
+// workgroup only, so the loads of the next tile stay in flight across it.
+__device__ __forceinline__ void tile_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// XOR of the masks of the set bits of v (NB bits, starting at mask[from])
+template <int NB>
+__device__ __forceinline__ uint32_t mix(const SweepOp& op, int from, int v) {
+  uint32_t a = 0;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) a ^= ((v >> b) & 1) ? op.mask[from + b] : 0u;
+  return a;
+}
+
+__device__ __forceinline__ float2& amp(unsigned char* t, uint32_t byte) { return *reinterpret_cast<float2*>(t + byte); }
+
+// A K-qubit pass on the matrix cores.  A wave takes UPW whole units, or, when
+// the tile has fewer units than the workgroup waves, WPU waves share a unit
+// and split its output rows (all of them read the unit before any writes it).
+template <int T, int NW, int K>
+__device__ __forceinline__ void op_mfma(unsigned char* tile, const SweepOp& op, const unsigned char* mats, int wave,
+                                        int lane) {
+  if constexpr (T >= K + 4) {
+    constexpr int IB = K - 2, N = 1 << IB, R = 2 * N, RT = N / 2;
+    constexpr int UB = T - K - 4, UNITS = 1 << UB;
+    constexpr int UPW = UNITS >= NW ? UNITS / NW : 1;
+    constexpr int WPU = UNITS >= NW ? 1 : (NW / UNITS < RT ? NW / UNITS : RT);
+    constexpr int RTW = RT / WPU;                   // row tiles per wave
+    constexpr int TB = UPW == 1 && RTW > 1 ? 2 : 1; // row tiles at a time
+    const bool on = wave < UNITS / UPW * WPU;
+    float b[UPW][R];
+    uint32_t up[UPW];
+    if (on) {
+      const uint32_t lp = mix<6>(op, IB, ((lane & 15) << 2) | (lane >> 4));
+#pragma unroll
+      for (int u = 0; u < UPW; ++u) {
+        up[u] = lp ^ mix<UB>(op, IB + 6, wave / WPU * UPW + u);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          const float2 v = amp(tile, up[u] ^ mix<IB>(op, 0, i));
+          b[u][2 * i] = v.x;
+          b[u][2 * i + 1] = v.y;
+        }
+      }
+    }
+    if constexpr (WPU > 1) tile_sync();
+    if (!on) return;
+    // row tile t, columns 2 i2, 2 i2 + 1 of this lane's h: (ur, ui) pairs of
+    // amplitude row (lane & 15) >> 1; rows come as (re, im) = (ur, -ui), (ui, ur)
+    const float4* A = reinterpret_cast<const float4*>(mats + op.mat) + ((lane >> 4) * 8 + ((lane & 15) >> 1));
+    const bool im = lane & 1;
+    const int t0 = (wave % WPU) * RTW;
+#pragma unroll
+    for (int tt = 0; tt < RTW; tt += TB) {
+      f32x4 acc[TB][UPW];
+#pragma unroll
+      for (int q = 0; q < TB; ++q)
+#pragma unroll
+        for (int u = 0; u < UPW; ++u) acc[q][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i2 = 0; i2 < N / 2; ++i2) {
+        float a[TB][4];
+#pragma unroll
+        for (int q = 0; q < TB; ++q) {
+          const float4 f = A[((t0 + tt + q) * (N / 2) + i2) * 32];
+          a[q][0] = im ? f.y : f.x;
+          a[q][1] = im ? f.x : -f.y;
+          a[q][2] = im ? f.w : f.z;
+          a[q][3] = im ? f.z : -f.w;
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int q = 0; q < TB; ++q)
+#pragma unroll
+            for (int u = 0; u < UPW; ++u)
+              acc[q][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][s], b[u][4 * i2 + s], acc[q][u], 0, 0, 0);
+      }
+#pragma unroll
+      for (int q = 0; q < TB; ++q)
+#pragma unroll
+        for (int u = 0; u < UPW; ++u)
+#pragma unroll
+          for (int w = 0; w < 2; ++w) {
+            // in-lane index 2 t + w; t0 is only known at run time when waves share a unit
+            const uint32_t at = up[u] ^ mix<IB>(op, 0, 2 * (t0 + tt + q) + w);
+            amp(tile, at) = make_float2(acc[q][u][2 * w], acc[q][u][2 * w + 1]);
+          }
+    }
+  }
+}
+
+// A pass of up to four qubits in the 3M form (kind 3; K = 4): T = Ur (Xr + Xi),
+// R = (Ur + Ui) Xi, I = (Ui - Ur) Xr, then Re = T - R, Im = T + I.  Lane (h, j)
+// holds amplitudes 4 h + i of group j; row 4 h + q of the product is one of them.
+template <int T, int NW>
+__device__ __forceinline__ void op_mfma3(unsigned char* tile, const SweepOp& op, const unsigned char* mats, int wave,
+                                         int lane) {
+  constexpr int UB = T - 8, UNITS = 1 << UB;
+  constexpr int UPW = UNITS >= NW ? UNITS / NW : 1;
+  constexpr int UC = UPW > 2 ? 2 : UPW;  // units at a time
+  if (wave >= UNITS / UPW) return;
+  const uint32_t lp = mix<6>(op, 2, ((lane & 15) << 2) | (lane >> 4));
+  const f32x4* A = reinterpret_cast<const f32x4*>(mats + op.mat) + lane;
+  const f32x4 ur = A[0], us = A[64], ud = A[128];
+  uint32_t up[UPW];
+  float2 v[UPW][4];
+#pragma unroll
+  for (int u = 0; u < UPW; ++u) {
+    up[u] = lp ^ mix<UB>(op, 8, wave * UPW + u);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[u][i] = amp(tile, up[u] ^ mix<2>(op, 0, i));
+  }
+#pragma unroll
+  for (int u0 = 0; u0 < UPW; u0 += UC) {
+    f32x4 t[UC], r[UC], m[UC];
+#pragma unroll
+    for (int u = 0; u < UC; ++u) t[u] = r[u] = m[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int u = 0; u < UC; ++u) {
+        t[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(ur[i], v[u0 + u][i].x + v[u0 + u][i].y, t[u], 0, 0, 0);
+        r[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(us[i], v[u0 + u][i].y, r[u], 0, 0, 0);
+        m[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(ud[i], v[u0 + u][i].x, m[u], 0, 0, 0);
+      }
+#pragma unroll
+    for (int u = 0; u < UC; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        amp(tile, up[u0 + u] ^ mix<2>(op, 0, q)) = make_float2(t[u][q] - r[u][q], t[u][q] + m[u][q]);
+  }
+}
+
+// A one- or two-qubit pass on the vector ALUs: local bits are in-lane bits.
+template <int T, int NW, int K>
+__device__ __forceinline__ void op_valu(unsigned char* tile, const SweepOp& op, const unsigned char* __restrict__ data,
+                                        int wave, int lane) {
+  constexpr int D = 1 << K;
+  constexpr int UNITS = 1 << (T - 8);
+  constexpr int UPW = UNITS >= NW ? UNITS / NW : 1;
+  if (wave * UPW >= UNITS) return;
+  const float2* __restrict__ U = reinterpret_cast<const float2*>(data + op.mat);
+  const uint32_t lp = mix<6>(op, 2, lane);
+  constexpr int UC = UPW > 2 ? 2 : UPW;  // units at a time
+#pragma unroll
+  for (int u0 = 0; u0 < UPW; u0 += UC) {
+    uint32_t up[UC];
+    float2 v[UC][4];
+#pragma unroll
+    for (int u = 0; u < UC; ++u) {
+      up[u] = lp ^ mix<T - 8>(op, 8, wave * UPW + u0 + u);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[u][i] = amp(tile, up[u] ^ mix<2>(op, 0, i));
+    }
+#pragma unroll
+    for (int u = 0; u < UC; ++u)
+#pragma unroll
+      for (int g = 0; g < 4; g += D)
+#pragma unroll
+        for (int r = 0; r < D; ++r) {
+          float2 o = make_float2(0.f, 0.f);
+#pragma unroll
+          for (int c = 0; c < D; ++c) cmac(o, U[r * D + c], v[u][g + c]);
+          amp(tile, up[u] ^ mix<2>(op, 0, g + r)) = o;
+        }
+  }
+}
+
+// A workgroup walks tiles blockIdx.x, blockIdx.x + gridDim.x, ...: the next
+// tile's loads are issued before the passes run on the current one, so memory
+// and the matrix cores work at the same time (with one tile per workgroup the
+// workgroups of a launch stayed in step, all loading and then all
+// multiplying).  The matrices of the k >= 3 passes are copied to LDS once.
+template <int T, int NW, bool NT>
+__global__ __launch_bounds__(64 * NW) void k_sweep(float4* __restrict__ psi, const unsigned char* __restrict__ data,
+                                                   const SweepArgs d) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  unsigned char* tile = smem;
+  unsigned char* mats = smem + ((size_t)8 << T);
+  constexpr int SLOTS = 1 << (T - 1);
+  constexpr int NTHR = 64 * NW;
+  constexpr int PER = SLOTS >= NTHR ? SLOTS / NTHR : 1;
+  const int tid = threadIdx.x;
+  const int L = d.low, nh = d.nh, nops = d.nops;
+  // first element of a tile: its number spread over the state bits outside it
+  auto first = [&](uint64_t t) {
+    uint64_t b = t << L, hi = d.hi;
+    for (int i = 0; i < nh; ++i, hi >>= 6) {
+      const uint64_t lm = ((uint64_t)1 << (hi & 63)) - 1;
+      b = ((b & ~lm) << 1) | (b & lm);
+    }
+    return b >> 1;
+  };
+  // amplitude offset of tile index x
+  auto spread = [&](uint32_t x) {
+    uint64_t o = x & ((1u << L) - 1);
+    uint64_t hi = d.hi;
+    for (int i = 0; i < nh; ++i, hi >>= 6) o |= (uint64_t)((x >> (L + i)) & 1) << (hi & 63);
+    return o;
+  };
+  const uint64_t own = spread(2 * tid) >> 1;
+  uint64_t off[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) off[i] = spread(2 * NTHR * i) >> 1;
+  float4* slots = reinterpret_cast<float4*>(tile);
+  const bool mine = SLOTS >= NTHR || tid < SLOTS;
+  const SweepOp* __restrict__ ops = reinterpret_cast<const SweepOp*>(data);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  float4 r[PER];
+  uint64_t t = blockIdx.x;
+  float4* cur = psi + first(t) + own;
+  if (mine) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) r[i] = gld<NT>(cur + off[i]);
+  }
+  {
+    const float4* from = reinterpret_cast<const float4*>(data + d.mat_off);
+    float4* to = reinterpret_cast<float4*>(mats);
+    for (int i = tid; i < d.mat16; i += NTHR) to[i] = from[i];
+  }
+  while (true) {
+    // a thread's slots are its own between the store and the next load
+    if (mine) {
+#pragma unroll
+      for (int i = 0; i < PER; ++i) slots[swz(tid + NTHR * i)] = r[i];
+    }
+    tile_sync();
+    const uint64_t tn = t + gridDim.x;
+    float4* next = psi + first(tn) + own;
+    if (mine && tn < d.tiles) {
+#pragma unroll
+      for (int i = 0; i < PER; ++i) r[i] = gld<NT>(next + off[i]);
+    }
+    SweepOp op = ops[0];
+    for (int o = 0; o < nops; ++o) {
+      const SweepOp ahead = ops[o + 1 < nops ? o + 1 : o];  // its scalar loads run beside this pass
+      switch (op.kind) {
+        case 1: op_valu<T, NW, 1>(tile, op, data, wave, lane); break;
+        case 2: op_valu<T, NW, 2>(tile, op, data, wave, lane); break;
+        case 3: op_mfma3<T, NW>(tile, op, mats, wave, lane); break;
+        case 4: op_mfma<T, NW, 4>(tile, op, mats, wave, lane); break;
+        case 5: op_mfma<T, NW, 5>(tile, op, mats, wave, lane); break;
+        case 6: op_mfma<T, NW, 6>(tile, op, mats, wave, lane); break;
+        default: break;  // kinds are set on the host
+      }
+      tile_sync();
+      op = ahead;
+    }
+    if (mine) {
+#pragma unroll
+      for (int i = 0; i < PER; ++i) gst<NT>(cur + off[i], slots[swz(tid + NTHR * i)]);
+    }
+    if (tn >= d.tiles) break;
+    t = tn;
+    cur = next;
+  }
+}
+
+constexpr uint64_t kSweepGroups = 512;  // workgroups of a launch: two per CU
+
+template <int T, int NW>
+void launch_t(const Sweep& sw, int n, void* psi, const unsigned char* data, hipStream_t st) {
+  const SweepArgs a = sweep_args(sw, n);
+  const dim3 grid((unsigned)(a.tiles < kSweepGroups ? a.tiles : kSweepGroups));
+  const size_t lds = ((size_t)8 << T) + sw.mat_bytes;
+  auto* kernel = n >= kNtMinQubits ? k_sweep<T, NW, true> : k_sweep<T, NW, false>;
+  if (lds > 65536)  // above the default limit of a workgroup's dynamic LDS
+    SV_HIP(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), lds, st, (float4*)psi, data, a);
+}
+
+}  // namespace
+
+void launch_sweep(const Sweep& sw, int n, void* psi, const unsigned char* data, hipStream_t st) {
+  if (sw.T > n) throw DeviceError{hipErrorInvalidValue, "k_sweep: tile larger than the state"};
+  switch (sw.T) {
+    case 8: launch_t<8, 8>(sw, n, psi, data, st); break;
+    case 9: launch_t<9, 8>(sw, n, psi, data, st); break;
+    case 10: launch_t<10, 8>(sw, n, psi, data, st); break;
+    case 11: launch_t<11, 8>(sw, n, psi, data, st); break;
+    case 12: launch_t<12, 8>(sw, n, psi, data, st); break;
+    case 13: launch_t<13, 8>(sw, n, psi, data, st); break;
+    default: throw DeviceError{hipErrorInvalidValue, "k_sweep: tile bits"};
+  }
+  SV_HIP(hipGetLastError());
+}
+
+}  // namespace sv

@@ -57,8 +57,7 @@ struct Pass {
   int s[SV_MAX_K] = {0, 0, 0, 0, 0, 0};  // sorted targets
   int variant = V_REG;                   // resolved (never AUTO)
   int precision = SV_PREC_FP32_VALU;
-  size_t mat_off = 0;                    // byte offset of the pass data in the matrix arena
-  size_t mat_bytes = 0;
+  size_t mat_bytes = 0;                  // bytes of the pass data
   // launch shape (from the tuner or defaults)
   int tile_bits = 13;                    // LDS: log2 amplitudes per tile
   int reg_iters = 1;                     // REG: groups per thread
@@ -84,7 +83,7 @@ struct Shape {
 };
 
 // Kernel launchers (k_apply.hip, k_mfma.hip, k_state.hip).
-void launch_pass(const Pass& p, int n, void* psi, const unsigned char* arena_dev, hipStream_t st);
+void launch_pass(const Pass& p, int n, void* psi, const unsigned char* data, hipStream_t st);  // data: the pass's own
 void launch_init_basis(void* psi, int n, uint64_t index, hipStream_t st);
 void launch_norm(const void* psi, int n, double* partials, int max_parts, double* out, hipStream_t st);
 int norm_partials_needed();

@@ -1,0 +1,188 @@
+// Host side of the tile sweeps (see sweep.h): which passes share a sweep, and
+// the device data of one.
+#include "sweep.h"
+
+#include <algorithm>
+#include <cstring>
+#include <stdexcept>
+
+namespace sv {
+
+namespace {
+// Device kind of a k-target pass: 1 and 2 on the vector ALUs; 3: up to four
+// targets in the 3M form (what the single register passes of FP32_VALU use at
+// these sizes); 4..6: the 4M form.  Kinds 3 and 4 pad k < 4 with identity bits.
+int op_kind(int k, int precision) {
+  if (k <= 2) return k;
+  return k <= 4 && precision != SV_PREC_FP32_MFMA ? 3 : std::max(k, 4);
+}
+int kind_bits(int kind) { return kind == 3 ? 4 : kind; }
+size_t op_mat_bytes(int kind) { return ((size_t)8 << (2 * kind_bits(kind))) / 2 * (kind == 3 ? 3 : 2); }
+size_t lds_mat_bytes(int kind) { return kind > 2 ? op_mat_bytes(kind) : 0; }
+
+// byte-address mask of tile bit b (the swizzle of k_sweep.hip on one bit)
+uint32_t bit_mask(int b) {
+  if (b == 0) return 8;
+  const int e = 1 << (b - 1);
+  return (uint32_t)((e ^ (((e >> 4) ^ (e >> 8)) & 15)) * 16);
+}
+}  // namespace
+
+// Tile size of an n-qubit state.
+int sweep_tile_bits(int n) {
+  return n <= 20 ? std::min(n, 12) : 13;
+}
+
+// The FP32 passes of every size (the split precisions keep their own kernels
+// for k >= 4), as long as the tile holds one unit of 16 groups.
+int sweep_kind(int n, int k, int precision) {
+  if (n < kSweepMinBits || std::max(k, 4) + 4 > sweep_tile_bits(n)) return 0;
+  if (k >= 4 && precision != SV_PREC_FP32_VALU && precision != SV_PREC_FP32_MFMA) return 0;
+  return op_kind(k, precision);
+}
+
+// Greedy in passes: a sweep is seeded with the first pass left and takes
+// every later eligible pass whose targets still fit in the tile and which
+// shares no qubit with a pass skipped before it (so it commutes with all of
+// those).  A pass that is not eligible is a sweep of its own (T = 0) and keeps
+// its place in the order.
+void plan_sweeps(const std::vector<SweepItem>& items, int n, std::vector<Sweep>& out) {
+  out.clear();
+  const int T = sweep_tile_bits(n);
+  const int low = T == n ? T : kSweepLow;
+  const uint64_t low_mask = ((uint64_t)1 << low) - 1;
+  std::vector<char> used(items.size(), 0);
+  for (size_t s = 0; s < items.size(); ++s) {
+    if (used[s]) continue;
+    Sweep sw;
+    sw.members.push_back((int)s);
+    used[s] = 1;
+    if (items[s].kind) {
+      sw.T = T;
+      sw.low = low;
+      sw.bits = low_mask | items[s].mask;
+      size_t mat = lds_mat_bytes(items[s].kind);
+      sw.data_bytes = sizeof(SweepOp) + op_mat_bytes(items[s].kind);
+      uint64_t blocked = 0;
+      for (size_t h = s + 1; h < items.size(); ++h) {
+        if (used[h]) continue;
+        const uint64_t m = items[h].mask;
+        const size_t mb = lds_mat_bytes(items[h].kind);
+        if (items[h].kind && (m & blocked) == 0 && __builtin_popcountll(sw.bits | m) <= T &&
+            mat + mb <= sweep_mat_room(T)) {
+          sw.bits |= m;
+          mat += mb;
+          sw.data_bytes += sizeof(SweepOp) + op_mat_bytes(items[h].kind);
+          sw.members.push_back((int)h);
+          used[h] = 1;
+        } else {
+          blocked |= m;
+          if ((sw.bits & ~blocked) == 0 && __builtin_popcountll(sw.bits) == T) break;  // nothing more can join
+        }
+      }
+      sw.mat_bytes = mat;
+      // fill the tile with the lowest bits left
+      for (int b = low; b < n && __builtin_popcountll(sw.bits) < T; ++b) sw.bits |= (uint64_t)1 << b;
+    }
+    out.push_back(std::move(sw));
+  }
+}
+
+SweepArgs sweep_args(const Sweep& sw, int n) {
+  SweepArgs a;
+  a.tiles = (uint64_t)1 << (n - sw.T);
+  a.low = sw.low;
+  for (int b = sw.low; b < n; ++b)
+    if ((sw.bits >> b) & 1) a.hi |= (uint64_t)b << (6 * a.nh++);
+  a.nops = (int32_t)sw.members.size();
+  a.mat16 = (int32_t)(sw.mat_bytes / 16);
+  a.mat_off = (uint32_t)(sw.data_bytes - sw.mat_bytes);
+  return a;
+}
+
+void encode_sweep(const Sweep& sw, const std::vector<const Pass*>& passes, const std::vector<const double*>& mats,
+                  unsigned char* dst) {
+  int tile_bit[64], tb = 0;
+  for (int b = 0; b < 64; ++b) tile_bit[b] = (sw.bits >> b) & 1 ? tb++ : -1;
+  // the passes, the matrices of kinds 1 and 2, then the block that goes to LDS
+  size_t at = passes.size() * sizeof(SweepOp), big = 0;
+  const size_t big_off = sw.data_bytes - sw.mat_bytes;
+  for (size_t p = 0; p < passes.size(); ++p) {
+    const Pass& ps = *passes[p];
+    const int k = ps.k, kind = op_kind(k, ps.precision), K = kind_bits(kind);
+    SweepOp op{};
+    op.kind = (uint32_t)kind;
+    op.mat = (uint32_t)(K <= 2 ? at : big);
+    // roles of the tile bits: the local bits (targets, then identity bits),
+    // lane bits, unit bits.  The lane bits j, and with them h, should fall on
+    // different banks: bit 0 and tile bits b with different (b - 1) % 4.
+    const int nl = std::max(K, 2);  // in-lane and h bits for K >= 4; the two in-lane bits for K <= 2
+    bool taken[kSweepMaxBits] = {};
+    int role[kSweepMaxBits], nr = 0;
+    for (int j = 0; j < k; ++j) {
+      role[nr++] = tile_bit[ps.s[j]];
+      taken[role[nr - 1]] = true;
+    }
+    auto cls = [](int b) { return b == 0 ? 4 : (b - 1) & 3; };
+    for (int b = sw.T - 1; b >= 0 && nr < nl; --b)  // identity bits from the top
+      if (!taken[b]) taken[role[nr++] = b] = true;
+    bool cls_used[5] = {};
+    const int lanes = K <= 2 ? 6 : 4;
+    if (K >= 4) cls_used[cls(role[K - 2])] = true;  // h bit 0
+    int got = 0;
+    for (int pass = 0; pass < 2 && got < lanes; ++pass)  // distinct classes first, then any
+      for (int b = 0; b < sw.T && got < lanes; ++b) {
+        if (taken[b] || (pass == 0 && cls_used[cls(b)])) continue;
+        cls_used[cls(b)] = true;
+        taken[b] = true;
+        role[nr++] = b;
+        ++got;
+      }
+    for (int b = 0; b < sw.T; ++b)
+      if (!taken[b]) role[nr++] = b;
+    for (int b = 0; b < sw.T; ++b) op.mask[b] = bit_mask(role[b]);
+    std::memcpy(dst + p * sizeof(SweepOp), &op, sizeof(op));
+    const double* m = mats[p];
+    float* f = reinterpret_cast<float*>(dst + (K <= 2 ? at : big_off + big));
+    (K <= 2 ? at : big) += op_mat_bytes(kind);
+    if (K <= 2) {
+      for (size_t e = 0; e < (size_t)2 << (2 * K); ++e) f[e] = (float)m[e];
+      continue;
+    }
+    if (kind == 3) {
+      // [ur, ur + ui, ui - ur][h][row][i]: lane h holds amplitudes 4 h + i
+      for (int lane = 0; lane < 64; ++lane)
+        for (int i = 0; i < 4; ++i) {
+          const int row = lane & 15, col = (lane >> 4) * 4 + i;
+          double ur = 0.0, ui = 0.0;
+          if ((row >> k) == (col >> k)) {  // identity on the padding bits
+            const size_t e = (size_t)2 * ((row & ((1 << k) - 1)) * (1 << k) + (col & ((1 << k) - 1)));
+            ur = m[e];
+            ui = m[e + 1];
+          }
+          f[lane * 4 + i] = (float)ur;
+          f[256 + lane * 4 + i] = (float)(ur + ui);
+          f[512 + lane * 4 + i] = (float)(ui - ur);
+        }
+      continue;
+    }
+    // [row tile t][column pair i2][h][row r of 8]: lane h holds the
+    // amplitudes h N + i; row r of tile t is amplitude (r / 2) N + 2 t + r % 2
+    const int N = 1 << (K - 2), dk = 1 << k;
+    for (int t = 0; t < N / 2; ++t)
+      for (int i2 = 0; i2 < N / 2; ++i2)
+        for (int h = 0; h < 4; ++h)
+          for (int r = 0; r < 8; ++r)
+            for (int w = 0; w < 2; ++w, f += 2) {
+              const int row = (r >> 1) * N + 2 * t + (r & 1), col = h * N + 2 * i2 + w;
+              f[0] = f[1] = 0.f;
+              if ((row >> k) != (col >> k)) continue;  // identity on the padding bits
+              const size_t e = (size_t)2 * ((row & (dk - 1)) * dk + (col & (dk - 1)));
+              f[0] = (float)m[e];
+              f[1] = (float)m[e + 1];
+            }
+  }
+  if (at != big_off || big != sw.mat_bytes) throw std::logic_error("sweep matrices do not match their plan");
+}
+
+}  // namespace sv

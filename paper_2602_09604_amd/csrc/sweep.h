@@ -1,0 +1,71 @@
+// Sweeps: several consecutive matrix passes applied in one trip through
+// memory.  A workgroup stages a tile of 2^T amplitudes in LDS (the L lowest
+// state bits plus T - L chosen higher bits), applies every pass of the sweep
+// whose targets lie in the tile to it, one after another, and writes the tile
+// back.  sweep.cpp plans and encodes sweeps, k_sweep.hip runs them.
+#pragma once
+#include "sv_internal.h"
+
+namespace sv {
+
+constexpr int kSweepMaxBits = 13;  // largest tile: 2^13 amplitudes, 64 KiB of LDS
+constexpr int kSweepMinBits = 8;   // one matrix-core unit of a k = 4 pass
+// LDS for the matrices of a sweep: two workgroups share a CU's 160 KiB (a
+// sweep of one larger matrix takes more and runs alone).
+constexpr size_t sweep_mat_room(int T) { return 81920 - ((size_t)8 << T); }
+constexpr int kSweepLow = 4;       // low state bits in every tile: whole 128-byte lines
+constexpr int kSweepMaxK = 6;
+
+// One pass of a sweep on the device.  Tile bits are numbered in the order
+// in-lane bits (K - 2 of them; for K = 2 both local bits), two lane bits h,
+// four lane bits j, then unit bits; mask[b] is what bit b adds (by XOR) to a
+// byte address in the tile: the swizzle of the tile's slots is linear over
+// the bits, so any assignment of state bits to these roles is one table.
+struct alignas(64) SweepOp {
+  uint32_t mask[kSweepMaxBits];
+  uint32_t kind;   // 1, 2: vector ALUs; 3: matrix cores, 3M form of up to 4 qubits; 4..6: 4M form
+  uint32_t mat;    // byte offset of the matrix: kinds 1, 2 from the sweep's data, the others in the LDS copy
+};
+
+// Launch arguments of a sweep.  hi packs the state bits of the tile above its
+// L low bits, ascending, six bits each: tile bit L + i is state bit
+// (hi >> 6 i) & 63.
+struct SweepArgs {
+  uint64_t tiles = 0;
+  uint64_t hi = 0;
+  int32_t low = 0;      // L
+  int32_t nh = 0;       // T - L
+  int32_t nops = 0;
+  int32_t mat16 = 0;    // LDS copy of the matrices of kinds 3..6, in 16-byte units
+  uint32_t mat_off = 0; // where they start in the data (the passes come first)
+};
+
+// A planned sweep: its tile and its passes (in order), indices into the
+// caller's list.
+struct Sweep {
+  int T = 0;
+  int low = 0;
+  uint64_t bits = 0;            // state bits in the tile
+  std::vector<int> members;
+  size_t mat_bytes = 0;         // LDS bytes of the matrices
+  size_t data_bytes = 0;        // device data: the passes and every matrix
+};
+
+// A pass as the planner sees it: its qubits and its kind (0: not for a sweep).
+struct SweepItem {
+  uint64_t mask = 0;
+  int kind = 0;
+};
+
+int sweep_tile_bits(int n);
+// Device kind of a k-target pass in a sweep of an n-qubit state; 0: it does
+// not run in one.
+int sweep_kind(int n, int k, int precision);
+void plan_sweeps(const std::vector<SweepItem>& items, int n, std::vector<Sweep>& out);
+SweepArgs sweep_args(const Sweep& sw, int n);
+// Encode one sweep: targets (sorted) and matrix of every pass, in order.
+void encode_sweep(const Sweep& sw, const std::vector<const Pass*>& passes, const std::vector<const double*>& mats,
+                  unsigned char* dst);
+void launch_sweep(const Sweep& sw, int n, void* psi, const unsigned char* data, hipStream_t st);
+
+}  // namespace sv

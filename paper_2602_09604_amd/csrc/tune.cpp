@@ -140,7 +140,6 @@ int sv_autotune(sv_state* s, int budget_ms) {
               p.tile_bits = cand.second;
               p.mfma_x = p.variant == V_MFMA ? mfma_exchange_mask(n, p) : 0;
               p.mat_bytes = pass_data_bytes(p);
-              p.mat_off = 0;
               encode_pass_data(p, mat.data(), host);
               SV_HIP(hipMemcpyAsync(dev, host, p.mat_bytes, hipMemcpyHostToDevice, st));
               launch_pass(p, n, psi, dev, st);  // warm-up
