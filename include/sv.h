@@ -47,10 +47,12 @@ extern "C" {
 /* ---- enumerations ------------------------------------------------------- */
 #define SV_C64 0              /* state dtype: complex64 (the only one built) */
 
-/* Arithmetic of a pass.  FP32_VALU: every pass on vector FP32 FMAs
- * (register passes with at most four targets besides bit 0 multiply in the
- * 3M form, three real products per complex multiply-accumulate, with the
- * matrix's ur + ui and ui - ur formed in FP64).
+/* Arithmetic of a pass.  FP32_VALU: FP32 products and sums, on the vector
+ * ALUs for a pass launched by itself with k <= 4 (register passes with at most
+ * four targets besides bit 0 multiply in the 3M form, three real products per
+ * complex multiply-accumulate, with the matrix's ur + ui and ui - ur formed
+ * in FP64), and on the FP32 matrix cores, in FP32_MFMA's 4M form, for k >= 5
+ * and for the k >= 3 passes of a tile sweep.
  * FP32_MFMA: passes with k >= 4 as a real GEMM in the 4M form
  * [Yr;Yi] = [[Ur,-Ui],[Ui,Ur]] [Xr;Xi] on FP32 matrix cores.
  * BF16X3 / FP16X3: the same GEMM with every operand split into hi + lo
@@ -150,7 +152,7 @@ typedef struct {
 
 typedef struct {
   uint64_t gates_in;     /* gates given */
-  uint64_t passes;       /* fused passes launched */
+  uint64_t passes;       /* fused passes applied */
   uint64_t bytes;        /* algorithmic HBM bytes: 16 * 2^n per pass, 16 * 2^(n-c)
                             for a controlled pass with c controls; for sv_batch_run
                             16 * 2^n per LDS-resident circuit (one read, one write)
@@ -167,8 +169,9 @@ typedef struct {
                                  graph without capturing a new one */
   uint64_t variant_bytes[5];  /* with opts.timing: algorithmic bytes per kernel family */
   uint64_t launches;          /* kernel launches the call issued (inside its graph when it
-                                 ran as one): one per pass for sv_apply_circuit; for
-                                 sv_batch_run one LDS-resident launch plus one per level */
+                                 ran as one): at most one per pass, fewer when several
+                                 passes run as one tile sweep; for sv_batch_run one per
+                                 sweep level (and one for circuits no tile takes) */
 } sv_run_stats;
 
 /* ---- state -------------------------------------------------------------- */
@@ -215,9 +218,12 @@ int sv_apply_controlled_gate(sv_state* s, const int32_t* qubits, int k, const do
                              const int32_t* controls, const int32_t* control_values);
 
 /* Apply a circuit: validate all gates, fuse them per opts (FP64 on the host),
- * round each fused matrix once to the pass precision, upload every matrix
- * with one host-to-device copy, then launch one in-place pass per fused gate
- * (as one hipGraph when opts->use_graph).  opts NULL means {max_k 4, GREEDY,
+ * round each fused matrix once to the pass precision, upload the matrices,
+ * then apply one in-place pass per fused gate (as one hipGraph when
+ * opts->use_graph).  Passes that fit together in a tile of the state held in
+ * LDS share one read and write of it (a tile sweep), each still applied by
+ * itself and in an order the circuit allows; with a forced variant or timing
+ * every pass is a launch of its own.  opts NULL means {max_k 4, GREEDY,
  * FP32_VALU, no graph, AUTO}.  FUSE_NONE + FP32_VALU is the plain unfused
  * FP32 baseline: same kernels, one pass per gate.  When stats is not NULL the
  * call waits for the passes and fills it; otherwise it returns once the work
@@ -316,17 +322,14 @@ int sv_write_amplitudes(sv_state* s, uint64_t start, uint64_t count, const float
  * batch, with each circuit fused as in Sec. II-C.  Runs n_circuits circuits,
  * circuit c on states[c] (each handle on the same device).  The work is
  * queued on the stream of states[0], after the work already queued on the
- * other handles' streams; the call returns once it has finished.  All
- * launches are captured in one hipGraph: circuits whose state fits in LDS
- * (n <= the autotuned limit: at most 14 qubits = 128 KiB, and no more than
- * the device's LDS per workgroup) run in one workgroup each, entirely on
- * chip, with one HBM read and one write;
- * larger ones advance one fused pass per launch of a level kernel that
- * covers that pass of every circuit that has one (the kernel boundary is
- * the barrier between a circuit's dependent passes).  On a device failure
- * every handle in the batch is poisoned.  Gates are fused first per opts (fusion mode and max_k; GREEDY
- * with max_k 4 when opts is NULL; the precision is always FP32), circuits on
- * host threads.  A controlled gate wider than max_k with its controls is
+ * other handles' streams; the call returns once it has finished.  Circuits
+ * run as tile sweeps (several fused passes on a tile of at most 2^12
+ * amplitudes staged in LDS; a state of up to 12 qubits is one tile), one
+ * launch per sweep level covering that sweep of every circuit that has one
+ * (the kernel boundary is the barrier between a circuit's dependent sweeps).
+ * On a device failure every handle in the batch is poisoned.  Gates are fused
+ * first per opts (fusion mode and max_k; GREEDY with max_k 4 when opts is
+ * NULL; the precision is always FP32), circuits on host threads.  A controlled gate wider than max_k with its controls is
  * rejected (SV_EINVAL).  States of at most 30 qubits.  When stats is not NULL
  * the call waits and fills it.  Equivalent to sv_apply_circuit on each state
  * in turn. */

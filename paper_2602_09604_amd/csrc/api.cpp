@@ -305,16 +305,17 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
   std::vector<Launch> launches;
   {
     const bool sweeps = !timing && o.variant == SV_VARIANT_AUTO && s->n >= kSweepMinBits;
+    const int T = sweep_tile_bits(s->n);
     std::vector<SweepItem> items(passes.size());
     for (size_t i = 0; i < passes.size(); ++i) {
       const Pass& p = passes[i];
       items[i].mask = p.cmask;
       for (int j = 0; j < p.k; ++j) items[i].mask |= (uint64_t)1 << p.s[j];
       if (p.variant == V_PHASE) items[i].mask = ~(uint64_t)0;
-      if (sweeps && p.variant != V_PHASE && !p.cmask) items[i].kind = sweep_kind(s->n, p.k, p.precision);
+      if (sweeps && p.variant != V_PHASE && !p.cmask) items[i].kind = sweep_kind(T, p.k, p.precision);
     }
     std::vector<Sweep> plan;
-    plan_sweeps(items, s->n, plan);
+    plan_sweeps(items, s->n, T, sweep_mat_room(T, T == s->n), plan);
     launches.resize(plan.size());
     for (size_t i = 0; i < plan.size(); ++i) launches[i].sweep = std::move(plan[i]);
   }
@@ -1061,6 +1062,12 @@ int state_n(sv_state* s) { return s->n; }
 hipStream_t state_stream(sv_state* s) { return s->stream; }
 bool state_poisoned(sv_state* s) { return s->poisoned; }
 void state_poison(sv_state* s) { s->poisoned = true; }
+// `bytes` of the handle's staging ring: pinned host memory and its device copy.
+void state_staging(sv_state* s, size_t bytes, unsigned char** host, unsigned char** dev) {
+  const size_t at = arena_take(s, bytes);
+  *host = s->arena_host + at;
+  *dev = s->arena_dev + at;
+}
 // After a batched run: a circuit with a gate that is not unitary leaves the
 // state's norm unknown to the host.
 void state_note_gates(sv_state* s, const sv_gate* g, size_t n) {

@@ -119,48 +119,6 @@ __device__ __forceinline__ void op_mfma(unsigned char* tile, const SweepOp& op, 
   }
 }
 
-// A pass of up to four qubits in the 3M form (kind 3; K = 4): T = Ur (Xr + Xi),
-// R = (Ur + Ui) Xi, I = (Ui - Ur) Xr, then Re = T - R, Im = T + I.  Lane (h, j)
-// holds amplitudes 4 h + i of group j; row 4 h + q of the product is one of them.
-template <int T, int NW>
-__device__ __forceinline__ void op_mfma3(unsigned char* tile, const SweepOp& op, const unsigned char* mats, int wave,
-                                         int lane) {
-  constexpr int UB = T - 8, UNITS = 1 << UB;
-  constexpr int UPW = UNITS >= NW ? UNITS / NW : 1;
-  constexpr int UC = UPW > 2 ? 2 : UPW;  // units at a time
-  if (wave >= UNITS / UPW) return;
-  const uint32_t lp = mix<6>(op, 2, ((lane & 15) << 2) | (lane >> 4));
-  const f32x4* A = reinterpret_cast<const f32x4*>(mats + op.mat) + lane;
-  const f32x4 ur = A[0], us = A[64], ud = A[128];
-  uint32_t up[UPW];
-  float2 v[UPW][4];
-#pragma unroll
-  for (int u = 0; u < UPW; ++u) {
-    up[u] = lp ^ mix<UB>(op, 8, wave * UPW + u);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[u][i] = amp(tile, up[u] ^ mix<2>(op, 0, i));
-  }
-#pragma unroll
-  for (int u0 = 0; u0 < UPW; u0 += UC) {
-    f32x4 t[UC], r[UC], m[UC];
-#pragma unroll
-    for (int u = 0; u < UC; ++u) t[u] = r[u] = m[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int u = 0; u < UC; ++u) {
-        t[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(ur[i], v[u0 + u][i].x + v[u0 + u][i].y, t[u], 0, 0, 0);
-        r[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(us[i], v[u0 + u][i].y, r[u], 0, 0, 0);
-        m[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(ud[i], v[u0 + u][i].x, m[u], 0, 0, 0);
-      }
-#pragma unroll
-    for (int u = 0; u < UC; ++u)
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        amp(tile, up[u0 + u] ^ mix<2>(op, 0, q)) = make_float2(t[u][q] - r[u][q], t[u][q] + m[u][q]);
-  }
-}
-
 // A one- or two-qubit pass on the vector ALUs: local bits are in-lane bits.
 template <int T, int NW, int K>
 __device__ __forceinline__ void op_valu(unsigned char* tile, const SweepOp& op, const unsigned char* __restrict__ data,
@@ -196,15 +154,14 @@ __device__ __forceinline__ void op_valu(unsigned char* tile, const SweepOp& op, 
   }
 }
 
-// A workgroup walks tiles blockIdx.x, blockIdx.x + gridDim.x, ...: the next
+// A workgroup walks tiles t, t + stride, ...: the next
 // tile's loads are issued before the passes run on the current one, so memory
 // and the matrix cores work at the same time (with one tile per workgroup the
 // workgroups of a launch stayed in step, all loading and then all
 // multiplying).  The matrices of the k >= 3 passes are copied to LDS once.
 template <int T, int NW, bool NT>
-__global__ __launch_bounds__(64 * NW) void k_sweep(float4* __restrict__ psi, const unsigned char* __restrict__ data,
-                                                   const SweepArgs d) {
-  extern __shared__ __align__(16) unsigned char smem[];
+__device__ __forceinline__ void sweep_tiles(float4* __restrict__ psi, const unsigned char* __restrict__ data,
+                                            const SweepArgs& d, uint64_t t, uint64_t stride, unsigned char* smem) {
   unsigned char* tile = smem;
   unsigned char* mats = smem + ((size_t)8 << T);
   constexpr int SLOTS = 1 << (T - 1);
@@ -237,7 +194,6 @@ __global__ __launch_bounds__(64 * NW) void k_sweep(float4* __restrict__ psi, con
   const SweepOp* __restrict__ ops = reinterpret_cast<const SweepOp*>(data);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   float4 r[PER];
-  uint64_t t = blockIdx.x;
   float4* cur = psi + first(t) + own;
   if (mine) {
 #pragma unroll
@@ -255,7 +211,7 @@ __global__ __launch_bounds__(64 * NW) void k_sweep(float4* __restrict__ psi, con
       for (int i = 0; i < PER; ++i) slots[swz(tid + NTHR * i)] = r[i];
     }
     tile_sync();
-    const uint64_t tn = t + gridDim.x;
+    const uint64_t tn = t + stride;
     float4* next = psi + first(tn) + own;
     if (mine && tn < d.tiles) {
 #pragma unroll
@@ -267,7 +223,6 @@ __global__ __launch_bounds__(64 * NW) void k_sweep(float4* __restrict__ psi, con
       switch (op.kind) {
         case 1: op_valu<T, NW, 1>(tile, op, data, wave, lane); break;
         case 2: op_valu<T, NW, 2>(tile, op, data, wave, lane); break;
-        case 3: op_mfma3<T, NW>(tile, op, mats, wave, lane); break;
         case 4: op_mfma<T, NW, 4>(tile, op, mats, wave, lane); break;
         case 5: op_mfma<T, NW, 5>(tile, op, mats, wave, lane); break;
         case 6: op_mfma<T, NW, 6>(tile, op, mats, wave, lane); break;
@@ -283,6 +238,38 @@ __global__ __launch_bounds__(64 * NW) void k_sweep(float4* __restrict__ psi, con
     if (tn >= d.tiles) break;
     t = tn;
     cur = next;
+  }
+}
+
+template <int T, int NW, bool NT>
+__global__ __launch_bounds__(64 * NW) void k_sweep(float4* __restrict__ psi, const unsigned char* __restrict__ data,
+                                                   const SweepArgs d) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  sweep_tiles<T, NW, NT>(psi, data, d, blockIdx.x, gridDim.x, smem);
+}
+
+// The same sweeps of many states in one launch: entry e of the table owns
+// workgroups first[e] .. first[e + 1) - 1.  Tiles of at most 2^12 amplitudes.
+template <bool NT>
+__global__ __launch_bounds__(512) void k_sweep_batch(const unsigned char* __restrict__ data,
+                                                     const BatchSweep* __restrict__ table, int count) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const uint32_t b = blockIdx.x;
+  int lo = 0, hi = count - 1;  // last entry with first <= b
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (table[mid].first <= b) lo = mid;
+    else hi = mid - 1;
+  }
+  const BatchSweep e = table[lo];
+  const uint64_t t = b - e.first;
+  switch (e.T) {
+    case 8: sweep_tiles<8, 8, NT>(e.psi, data + e.data, e.args, t, e.groups, smem); break;
+    case 9: sweep_tiles<9, 8, NT>(e.psi, data + e.data, e.args, t, e.groups, smem); break;
+    case 10: sweep_tiles<10, 8, NT>(e.psi, data + e.data, e.args, t, e.groups, smem); break;
+    case 11: sweep_tiles<11, 8, NT>(e.psi, data + e.data, e.args, t, e.groups, smem); break;
+    case 12: sweep_tiles<12, 8, NT>(e.psi, data + e.data, e.args, t, e.groups, smem); break;
+    default: break;  // tile sizes are set on the host
   }
 }
 
@@ -312,6 +299,15 @@ void launch_sweep(const Sweep& sw, int n, void* psi, const unsigned char* data, 
     case 13: launch_t<13, 8>(sw, n, psi, data, st); break;
     default: throw DeviceError{hipErrorInvalidValue, "k_sweep: tile bits"};
   }
+  SV_HIP(hipGetLastError());
+}
+
+void launch_sweep_batch(const BatchSweep* table, int count, unsigned groups, size_t lds, bool nt,
+                        const unsigned char* data, hipStream_t st) {
+  auto* kernel = nt ? k_sweep_batch<true> : k_sweep_batch<false>;
+  if (lds > 65536)
+    SV_HIP(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL(kernel, dim3(groups), dim3(512), lds, st, data, table, count);
   SV_HIP(hipGetLastError());
 }
 

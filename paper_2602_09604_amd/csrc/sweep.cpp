@@ -9,15 +9,10 @@
 namespace sv {
 
 namespace {
-// Device kind of a k-target pass: 1 and 2 on the vector ALUs; 3: up to four
-// targets in the 3M form (what the single register passes of FP32_VALU use at
-// these sizes); 4..6: the 4M form.  Kinds 3 and 4 pad k < 4 with identity bits.
-int op_kind(int k, int precision) {
-  if (k <= 2) return k;
-  return k <= 4 && precision != SV_PREC_FP32_MFMA ? 3 : std::max(k, 4);
-}
-int kind_bits(int kind) { return kind == 3 ? 4 : kind; }
-size_t op_mat_bytes(int kind) { return ((size_t)8 << (2 * kind_bits(kind))) / 2 * (kind == 3 ? 3 : 2); }
+// Device kind of a k-target pass: 1 and 2 on the vector ALUs, 4..6 on the
+// matrix cores (k = 3 padded with an identity bit).
+int op_kind(int k) { return k <= 2 ? k : std::max(k, 4); }
+size_t op_mat_bytes(int kind) { return (size_t)8 << (2 * kind); }  // complex64
 size_t lds_mat_bytes(int kind) { return kind > 2 ? op_mat_bytes(kind) : 0; }
 
 // byte-address mask of tile bit b (the swizzle of k_sweep.hip on one bit)
@@ -35,10 +30,10 @@ int sweep_tile_bits(int n) {
 
 // The FP32 passes of every size (the split precisions keep their own kernels
 // for k >= 4), as long as the tile holds one unit of 16 groups.
-int sweep_kind(int n, int k, int precision) {
-  if (n < kSweepMinBits || std::max(k, 4) + 4 > sweep_tile_bits(n)) return 0;
+int sweep_kind(int T, int k, int precision) {
+  if (std::max(k, 4) + 4 > T) return 0;
   if (k >= 4 && precision != SV_PREC_FP32_VALU && precision != SV_PREC_FP32_MFMA) return 0;
-  return op_kind(k, precision);
+  return op_kind(k);
 }
 
 // Greedy in passes: a sweep is seeded with the first pass left and takes
@@ -46,9 +41,8 @@ int sweep_kind(int n, int k, int precision) {
 // shares no qubit with a pass skipped before it (so it commutes with all of
 // those).  A pass that is not eligible is a sweep of its own (T = 0) and keeps
 // its place in the order.
-void plan_sweeps(const std::vector<SweepItem>& items, int n, std::vector<Sweep>& out) {
+void plan_sweeps(const std::vector<SweepItem>& items, int n, int T, size_t mat_room, std::vector<Sweep>& out) {
   out.clear();
-  const int T = sweep_tile_bits(n);
   const int low = T == n ? T : kSweepLow;
   const uint64_t low_mask = ((uint64_t)1 << low) - 1;
   std::vector<char> used(items.size(), 0);
@@ -69,7 +63,7 @@ void plan_sweeps(const std::vector<SweepItem>& items, int n, std::vector<Sweep>&
         const uint64_t m = items[h].mask;
         const size_t mb = lds_mat_bytes(items[h].kind);
         if (items[h].kind && (m & blocked) == 0 && __builtin_popcountll(sw.bits | m) <= T &&
-            mat + mb <= sweep_mat_room(T)) {
+            mat + mb <= mat_room) {
           sw.bits |= m;
           mat += mb;
           sw.data_bytes += sizeof(SweepOp) + op_mat_bytes(items[h].kind);
@@ -109,9 +103,9 @@ void encode_sweep(const Sweep& sw, const std::vector<const Pass*>& passes, const
   const size_t big_off = sw.data_bytes - sw.mat_bytes;
   for (size_t p = 0; p < passes.size(); ++p) {
     const Pass& ps = *passes[p];
-    const int k = ps.k, kind = op_kind(k, ps.precision), K = kind_bits(kind);
+    const int k = ps.k, K = op_kind(k);
     SweepOp op{};
-    op.kind = (uint32_t)kind;
+    op.kind = (uint32_t)K;
     op.mat = (uint32_t)(K <= 2 ? at : big);
     // roles of the tile bits: the local bits (targets, then identity bits),
     // lane bits, unit bits.  The lane bits j, and with them h, should fall on
@@ -144,26 +138,9 @@ void encode_sweep(const Sweep& sw, const std::vector<const Pass*>& passes, const
     std::memcpy(dst + p * sizeof(SweepOp), &op, sizeof(op));
     const double* m = mats[p];
     float* f = reinterpret_cast<float*>(dst + (K <= 2 ? at : big_off + big));
-    (K <= 2 ? at : big) += op_mat_bytes(kind);
+    (K <= 2 ? at : big) += op_mat_bytes(K);
     if (K <= 2) {
       for (size_t e = 0; e < (size_t)2 << (2 * K); ++e) f[e] = (float)m[e];
-      continue;
-    }
-    if (kind == 3) {
-      // [ur, ur + ui, ui - ur][h][row][i]: lane h holds amplitudes 4 h + i
-      for (int lane = 0; lane < 64; ++lane)
-        for (int i = 0; i < 4; ++i) {
-          const int row = lane & 15, col = (lane >> 4) * 4 + i;
-          double ur = 0.0, ui = 0.0;
-          if ((row >> k) == (col >> k)) {  // identity on the padding bits
-            const size_t e = (size_t)2 * ((row & ((1 << k) - 1)) * (1 << k) + (col & ((1 << k) - 1)));
-            ur = m[e];
-            ui = m[e + 1];
-          }
-          f[lane * 4 + i] = (float)ur;
-          f[256 + lane * 4 + i] = (float)(ur + ui);
-          f[512 + lane * 4 + i] = (float)(ui - ur);
-        }
       continue;
     }
     // [row tile t][column pair i2][h][row r of 8]: lane h holds the

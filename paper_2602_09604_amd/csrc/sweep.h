@@ -10,9 +10,10 @@ namespace sv {
 
 constexpr int kSweepMaxBits = 13;  // largest tile: 2^13 amplitudes, 64 KiB of LDS
 constexpr int kSweepMinBits = 8;   // one matrix-core unit of a k = 4 pass
-// LDS for the matrices of a sweep: two workgroups share a CU's 160 KiB (a
-// sweep of one larger matrix takes more and runs alone).
-constexpr size_t sweep_mat_room(int T) { return 81920 - ((size_t)8 << T); }
+// LDS for the matrices of a sweep: so that two workgroups share a CU's 160 KiB
+// (a sweep of one larger matrix takes more and runs alone), or, where the
+// state is a single tile, all of it.
+constexpr size_t sweep_mat_room(int T, bool one_tile) { return (one_tile ? 163840 : 81920) - ((size_t)8 << T); }
 constexpr int kSweepLow = 4;       // low state bits in every tile: whole 128-byte lines
 constexpr int kSweepMaxK = 6;
 
@@ -23,7 +24,7 @@ constexpr int kSweepMaxK = 6;
 // the bits, so any assignment of state bits to these roles is one table.
 struct alignas(64) SweepOp {
   uint32_t mask[kSweepMaxBits];
-  uint32_t kind;   // 1, 2: vector ALUs; 3: matrix cores, 3M form of up to 4 qubits; 4..6: 4M form
+  uint32_t kind;   // 1, 2: vector ALUs; 4..6: FP32 matrix cores
   uint32_t mat;    // byte offset of the matrix: kinds 1, 2 from the sweep's data, the others in the LDS copy
 };
 
@@ -36,7 +37,7 @@ struct SweepArgs {
   int32_t low = 0;      // L
   int32_t nh = 0;       // T - L
   int32_t nops = 0;
-  int32_t mat16 = 0;    // LDS copy of the matrices of kinds 3..6, in 16-byte units
+  int32_t mat16 = 0;    // LDS copy of the matrices of kinds 4..6, in 16-byte units
   uint32_t mat_off = 0; // where they start in the data (the passes come first)
 };
 
@@ -51,6 +52,17 @@ struct Sweep {
   size_t data_bytes = 0;        // device data: the passes and every matrix
 };
 
+// One sweep of one state of a batch: workgroups first .. first + groups - 1
+// of the launch walk its tiles.
+struct BatchSweep {
+  float4* psi;
+  uint64_t data;   // where its passes start in the batch's data
+  SweepArgs args;
+  uint32_t first;
+  uint32_t groups;
+  int32_t T;
+};
+
 // A pass as the planner sees it: its qubits and its kind (0: not for a sweep).
 struct SweepItem {
   uint64_t mask = 0;
@@ -58,14 +70,17 @@ struct SweepItem {
 };
 
 int sweep_tile_bits(int n);
-// Device kind of a k-target pass in a sweep of an n-qubit state; 0: it does
-// not run in one.
-int sweep_kind(int n, int k, int precision);
-void plan_sweeps(const std::vector<SweepItem>& items, int n, std::vector<Sweep>& out);
+// Device kind of a k-target pass in a sweep with tiles of T bits; 0: it does not run in one.
+int sweep_kind(int T, int k, int precision);
+// T: tile size, at most n; mat_room: LDS bytes for the matrices of a sweep.
+void plan_sweeps(const std::vector<SweepItem>& items, int n, int T, size_t mat_room, std::vector<Sweep>& out);
 SweepArgs sweep_args(const Sweep& sw, int n);
 // Encode one sweep: targets (sorted) and matrix of every pass, in order.
 void encode_sweep(const Sweep& sw, const std::vector<const Pass*>& passes, const std::vector<const double*>& mats,
                   unsigned char* dst);
 void launch_sweep(const Sweep& sw, int n, void* psi, const unsigned char* data, hipStream_t st);
+
+void launch_sweep_batch(const BatchSweep* table, int count, unsigned groups, size_t lds, bool nt,
+                        const unsigned char* data, hipStream_t st);
 
 }  // namespace sv

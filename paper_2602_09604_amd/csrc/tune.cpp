@@ -29,10 +29,6 @@ bool state_poisoned(sv_state* s);
 void state_poison(sv_state* s);
 int batch_lds_max_n();
 void set_batch_lds_max_n(int n);
-int batch_lds_cap();
-void batch_run_impl(void* const* psis, const int* ns, const sv_gate* const* circuits, const size_t* n_gates,
-                    size_t n_circ, const sv_run_opts& o, hipStream_t st, int lds_max_n, double* gpu_s,
-                    uint64_t* passes_out, double* fuse_s, uint64_t* bytes_out, uint64_t* launches_out);
 
 namespace {
 
@@ -169,71 +165,6 @@ int sv_autotune(sv_state* s, int budget_ms) {
     }
   done:
     SV_HIP(hipStreamSynchronize(st));
-    {
-      // Batched kernel: largest state kept LDS-resident.  A batch of 64
-      // two-layer RY-RZ + CNOT-ladder circuits per size, timed LDS-resident
-      // against level-synchronous sweeps; the limit grows while LDS wins.
-      const double pi = 3.14159265358979323846;
-      std::uniform_real_distribution<double> ang(0.0, 2 * pi);
-      int thr = 9;
-      for (int nb = 10; nb <= std::min(14, batch_lds_cap()); ++nb) {
-        const int copies = 64;
-        if (((size_t)copies << nb) > ((size_t)1 << n)) break;
-        std::vector<std::vector<double>> mats;
-        std::vector<sv_gate> gates;
-        for (int layer = 0; layer < 2; ++layer) {
-          for (int q = 0; q < nb; ++q) {
-            const double t = ang(rng), f = ang(rng);
-            mats.push_back({std::cos(t / 2), 0, -std::sin(t / 2), 0, std::sin(t / 2), 0, std::cos(t / 2), 0});
-            mats.push_back({std::cos(f / 2), -std::sin(f / 2), 0, 0, 0, 0, std::cos(f / 2), std::sin(f / 2)});
-          }
-          for (int q = 0; q + 1 < nb; ++q) {
-            std::vector<double> cx(32, 0.0);
-            cx[2 * 0] = cx[2 * (2 * 4 + 2)] = cx[2 * (3 * 4 + 1)] = cx[2 * (1 * 4 + 3)] = 1.0;
-            mats.push_back(cx);
-          }
-        }
-        size_t mi = 0;
-        for (int layer = 0; layer < 2; ++layer) {
-          for (int q = 0; q < nb; ++q)
-            for (int r = 0; r < 2; ++r) {
-              sv_gate g{};
-              g.k = 1;
-              g.qubits[0] = q;
-              g.matrix = mats[mi++].data();
-              gates.push_back(g);
-            }
-          for (int q = 0; q + 1 < nb; ++q) {
-            sv_gate g{};
-            g.k = 2;
-            g.qubits[0] = q;
-            g.qubits[1] = q + 1;
-            g.matrix = mats[mi++].data();
-            gates.push_back(g);
-          }
-        }
-        std::vector<void*> psis(copies);
-        std::vector<int> ns(copies, nb);
-        std::vector<const sv_gate*> circs(copies, gates.data());
-        std::vector<size_t> counts(copies, gates.size());
-        for (int c = 0; c < copies; ++c) psis[c] = (float2*)psi + ((size_t)c << nb);
-        sv_run_opts o{};
-        o.max_k = 4;
-        o.fusion = SV_FUSE_GREEDY;
-        double t_lds = 0, t_lvl = 0, best_lds = 1e30, best_lvl = 1e30;
-        for (int r = 0; r < 3; ++r) {
-          batch_run_impl(psis.data(), ns.data(), circs.data(), counts.data(), copies, o, st, 14, &t_lds, nullptr,
-                         nullptr, nullptr, nullptr);
-          batch_run_impl(psis.data(), ns.data(), circs.data(), counts.data(), copies, o, st, 0, &t_lvl, nullptr,
-                         nullptr, nullptr, nullptr);
-          best_lds = std::min(best_lds, t_lds);
-          best_lvl = std::min(best_lvl, t_lvl);
-        }
-        if (best_lds <= best_lvl) thr = nb;
-        else break;
-      }
-      set_batch_lds_max_n(thr);
-    }
     launch_init_basis(psi, n, 0, st);
     {
       std::lock_guard<std::mutex> lk(g_mu);
