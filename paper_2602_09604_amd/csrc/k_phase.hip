@@ -4,12 +4,11 @@
 // gates).  An elementwise, perfectly coalesced sweep: one read and one write
 // per amplitude, any number of interacting pairs in one pass.
 //
-// The grid covers a low span of 2^lb amplitudes (lb = min(n, 28)) and walks
+// The grid covers a low span of 2^lb amplitudes (phase_low_bits) and walks
 // it 2^(n - lb) times, once per value k of the high bits, so a thread's low
 // index bits never change.  (Measured at 34 qubits: spans of 2^21, 2^22,
 // 2^24, 2^26, 2^28, 2^30 amplitudes ran at 0.64, 0.67, 0.72, 0.74, 0.76,
-// 0.77 of HBM peak; the whole state as one span, 0.28 at 32 qubits, pays
-// the per-thread setup for every four amplitudes.)  Split x = xL + (k << lb):
+// 0.77 of HBM peak.)  Split x = xL + (k << lb):
 //   theta(x) = theta(xL) + theta_high(k) + sum_j k_j gamma_j(xL),
 //   gamma_j(xL) = sum_{a in L} beta_{a, lb+j} x_a.
 // A thread owns the amplitudes base + {0, 1, 512, 513} (bits 0 and 9 free in
@@ -87,21 +86,21 @@ __global__ __launch_bounds__(256) void k_phase(float4* __restrict__ psi, const u
   }
   // bit 9 exists only from 10 qubits up; its coefficients are zero below
   const double b09 = s_beta[9];
-  const float t00 = fold(th), t10 = fold(th + g0), t01 = fold(th + g9), t11 = fold(th + g0 + g9 + b09);
-  float gam[kPhaseMaxHigh];
+  const double t10 = th + g0, t01 = th + g9, t11 = th + g0 + g9 + b09;
+  double gam[kPhaseMaxHigh];
 #pragma unroll
   for (int j = 0; j < kPhaseMaxHigh; ++j) {
-    gam[j] = 0.f;
+    gam[j] = 0.0;
     if (j < a.nh) {
       const int b = a.lb + j;
       double r = s_rho[b];
       for (int q = 1; q < lq; ++q)
         if ((base >> q) & 1) r += s_beta[b * kPhaseMaxQ + q];
-      gam[j] = fold(r);
+      gam[j] = r;
     }
   }
 
-  const float4* tab = reinterpret_cast<const float4*>(data + kPhaseCoefBytes);
+  const double4* tab = reinterpret_cast<const double4*>(data + kPhaseCoefBytes);
   const uint64_t span = (uint64_t)1 << (a.lb - 1);  // elements per sweep of the grid
   const uint64_t sweeps = (uint64_t)1 << a.nh;
   const bool ok0 = e0 < a.pairs, ok1 = e0 + 256 < a.pairs;  // false only below 10 qubits
@@ -111,29 +110,29 @@ __global__ __launch_bounds__(256) void k_phase(float4* __restrict__ psi, const u
   // waits on the table
   float4 v0 = ok0 ? gld<NT>(psi + e0) : zero;
   float4 v1 = ok1 ? gld<NT>(psi + e0 + 256) : zero;
-  float4 hk = tab[0];
+  double4 hk = tab[0];
   for (uint64_t k = 0; k < sweeps; ++k) {
     const uint64_t f0 = e0 + k * span, f1 = f0 + 256;
-    float4 n0 = zero, n1 = zero, nk = zero;
+    float4 n0 = zero, n1 = zero;
+    double4 nk = hk;
     if (k + 1 < sweeps) {  // ok0 and ok1 hold whenever there is a next sweep
       n0 = gld<NT>(psi + f0 + span);
       n1 = gld<NT>(psi + f1 + span);
       nk = tab[k + 1];
     }
-    float G = hk.x;
+    // angles are summed in FP64 and rounded once, after the fold
+    double G = hk.x;
 #pragma unroll
-    for (int j = 0; j < kPhaseMaxHigh; ++j) {
+    for (int j = 0; j < kPhaseMaxHigh; ++j)
       if (j < a.nh && ((k >> j) & 1)) G += gam[j];
-      if ((j & 3) == 3) G -= rintf(G);  // keep the sum small: full FP32 resolution
-    }
     if (ok0) {
-      const float2 lo = rotate(make_float2(v0.x, v0.y), t00 + G);
-      const float2 hi = rotate(make_float2(v0.z, v0.w), t10 + G + hk.y);
+      const float2 lo = rotate(make_float2(v0.x, v0.y), fold(th + G));
+      const float2 hi = rotate(make_float2(v0.z, v0.w), fold(t10 + G + hk.y));
       gst<NT>(psi + f0, make_float4(lo.x, lo.y, hi.x, hi.y));
     }
     if (ok1) {
-      const float2 lo = rotate(make_float2(v1.x, v1.y), t01 + G + hk.z);
-      const float2 hi = rotate(make_float2(v1.z, v1.w), t11 + G + hk.y + hk.z);
+      const float2 lo = rotate(make_float2(v1.x, v1.y), fold(t01 + G + hk.z));
+      const float2 hi = rotate(make_float2(v1.z, v1.w), fold(t11 + G + hk.y + hk.z));
       gst<NT>(psi + f1, make_float4(lo.x, lo.y, hi.x, hi.y));
     }
     v0 = n0;

@@ -66,8 +66,7 @@ void PhasePoly::add_gate(int k, const int* q, const double* mat) {
 }
 
 void phase_data(const PhasePoly& p, int n, unsigned char* out) {
-  // angles in turns, folded into [-1/2, 1/2) (sums of a few stay small, so
-  // FP32 keeps ~2^-24 turn resolution on the device)
+  // angles in turns, folded into [-1/2, 1/2)
   auto turns = [](double a) {
     double t = wrap(a) / kTwoPi;
     return t >= 0.5 ? t - 1.0 : t;
@@ -83,7 +82,7 @@ void phase_data(const PhasePoly& p, int n, unsigned char* out) {
     for (int b = a + 1; b < m; ++b) beta[(size_t)a * kPhaseMaxQ + b] = beta[(size_t)b * kPhaseMaxQ + a] = turns(p.beta[a][b]);
   }
   const int lb = phase_low_bits(n), nh = n - lb;
-  float* tab = reinterpret_cast<float*>(out + kPhaseCoefBytes);
+  double* tab = reinterpret_cast<double*>(out + kPhaseCoefBytes);
   auto B = [&](int a, int b) { return beta[(size_t)a * kPhaseMaxQ + b]; };
   for (uint64_t k = 0; k < ((uint64_t)1 << nh); ++k) {
     double th = 0.0, b0 = 0.0, b9 = 0.0;
@@ -96,10 +95,10 @@ void phase_data(const PhasePoly& p, int n, unsigned char* out) {
       b0 += B(0, q);
       if (n > 9) b9 += B(9, q);
     }
-    tab[4 * k + 0] = (float)(th - std::nearbyint(th));
-    tab[4 * k + 1] = (float)(b0 - std::nearbyint(b0));
-    tab[4 * k + 2] = (float)(b9 - std::nearbyint(b9));
-    tab[4 * k + 3] = 0.f;
+    tab[4 * k + 0] = th - std::nearbyint(th);
+    tab[4 * k + 1] = b0 - std::nearbyint(b0);
+    tab[4 * k + 2] = b9 - std::nearbyint(b9);
+    tab[4 * k + 3] = 0.0;
   }
 }
 

@@ -187,15 +187,24 @@ struct PhasePoly {
 // [-1/2, 1/2)): the polynomial's coefficients as doubles -- c, alpha[q] and
 // beta[a][b] stored symmetrically, kPhaseMaxQ wide -- then, for the index
 // bits above the low span of 2^lb amplitudes one grid sweep covers
-// (lb = phase_low_bits(n)), one float4 per value k of those bits:
+// (lb = phase_low_bits(n)), four doubles per value k of those bits:
 // (theta_high(k), sum_j k_j beta[0][lb + j], sum_j k_j beta[9][lb + j], 0),
 // where theta_high is the polynomial on the high bits alone without c.
+// The low span is a sixteenth of the state, but 2^20 to 2^28 amplitudes: each
+// thread sets its own low part up once and then walks the sweeps, so with the
+// whole state as one span the setup is the pass (28 qubits: 1748 us, against
+// 789 us at 16 sweeps, 866 at 256), and below 2^20 too few threads are left
+// (26 qubits: 205 us at 2^22, 492 at 2^18).
 constexpr int kPhaseMaxQ = SV_MAX_QUBITS;
 constexpr int kPhaseLowBits = 28;
 constexpr int kPhaseMaxHigh = kPhaseMaxQ - kPhaseLowBits;
 constexpr size_t kPhaseCoefBytes = ((1 + kPhaseMaxQ + (size_t)kPhaseMaxQ * kPhaseMaxQ) * sizeof(double) + 15) / 16 * 16;
-inline int phase_low_bits(int n) { return n < kPhaseLowBits ? n : kPhaseLowBits; }
-inline size_t phase_data_bytes(int n) { return kPhaseCoefBytes + 16 * ((size_t)1 << (n - phase_low_bits(n))); }
+constexpr int kPhaseMinLowBits = 20;
+inline int phase_low_bits(int n) {
+  if (n <= kPhaseMinLowBits) return n;
+  return n - 4 < kPhaseMinLowBits ? kPhaseMinLowBits : n - 4 > kPhaseLowBits ? kPhaseLowBits : n - 4;
+}
+inline size_t phase_data_bytes(int n) { return kPhaseCoefBytes + 32 * ((size_t)1 << (n - phase_low_bits(n))); }
 void phase_data(const PhasePoly& p, int n, unsigned char* out);
 void launch_phase(int n, void* psi, const unsigned char* data, hipStream_t st);
 void launch_ctrl(const Pass& p, int n, void* psi, const float2* U, hipStream_t st);
