@@ -373,31 +373,45 @@ __global__ __launch_bounds__(kThreads) void k_marginal_partial(const float2* __r
 }
 
 // ------------------------------------------------------------------ sampling
-// 1. chunk sums of |c_i|^2 (one wave per chunk of 2^c amplitudes);
+// 1. sums of |c_i|^2 over chunks of 2^c amplitudes (one wave per chunk) and
+//    over the 2^b equal parts of each (up to eight parts of at least 512);
 // 2. inclusive prefix sums of the chunk sums (blocks of 2048, then the block
 //    totals, then the offsets added back);
-// 3. per shot (one wave): binary search for the first chunk whose inclusive
-//    prefix exceeds u * total, then a wave-wide inclusive scan through that
-//    chunk for the first amplitude that crosses the remainder.
+// 3. per shot, a binary search for the first chunk whose inclusive prefix
+//    exceeds u * total (one thread per shot);
+// 4. per shot (one wave), a scan over that chunk's parts and one over the
+//    part, eight amplitudes per lane, for the first amplitude that crosses
+//    the remainder.
+// A wave of step 4 is a chain of three dependent loads and reads 4 KB of the
+// state.  At 28 qubits and 100000 shots a wave that searched by itself and
+// stepped through the chunk 64 amplitudes at a time took 666 us; steps 3 and 4
+// take 9 + 108 us (159 with 8-byte loads in step 4), and the parts cost step 1
+// 12 us of 328.
 template <bool NT>
-__global__ __launch_bounds__(kThreads) void k_chunk_sums(const float2* __restrict__ psi, int cbits,
-                                                        uint64_t nchunks, double* __restrict__ sums) {
+__global__ __launch_bounds__(kThreads) void k_chunk_sums(const float2* __restrict__ psi, int cbits, int bbits,
+                                                        uint64_t nchunks, double* __restrict__ sums,
+                                                        double* __restrict__ parts) {
   const uint64_t ch = ((uint64_t)blockIdx.x * kThreads + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
   if (ch >= nchunks) return;  // whole waves leave together
   // 16-byte loads (two amplitudes per lane), several in flight: the sum
   // order per lane stays fixed (cbits >= 1, so a chunk is whole elements)
-  const uint64_t len4 = (uint64_t)1 << (cbits - 1);
+  const uint64_t len4 = (uint64_t)1 << (cbits - 1 - bbits);  // elements of a part
   const float4* __restrict__ p = reinterpret_cast<const float4*>(psi + (ch << cbits));
-  double v = 0.0;
-#pragma unroll 8
-  for (uint64_t i = lane; i < len4; i += 64) {
-    const float4 a = gld<NT>(p + i);
-    v += sq(make_float2(a.x, a.y));
-    v += sq(make_float2(a.z, a.w));
+  double total = 0.0;
+  for (int b = 0; b < 1 << bbits; ++b, p += len4) {
+    double v = 0.0;
+#pragma unroll 4
+    for (uint64_t i = lane; i < len4; i += 64) {
+      const float4 a = gld<NT>(p + i);
+      v += sq(make_float2(a.x, a.y));
+      v += sq(make_float2(a.z, a.w));
+    }
+    v = wave_sum(v);
+    if (lane == 0) parts[(ch << bbits) + b] = v;
+    total += v;
   }
-  v = wave_sum(v);
-  if (lane == 0) sums[ch] = v;
+  if (lane == 0) sums[ch] = total;
 }
 
 constexpr int kScanPer = 8;                       // elements per thread
@@ -455,21 +469,29 @@ __global__ __launch_bounds__(kThreads) void k_scan_add(double* __restrict__ x, u
 
 constexpr uint64_t kNoSample = ~(uint64_t)0;
 
-__global__ __launch_bounds__(kThreads) void k_sample(const float2* __restrict__ psi, int cbits,
-                                                    const double* __restrict__ incl, uint64_t nchunks,
-                                                    const double* __restrict__ u, uint64_t shots,
-                                                    uint64_t* __restrict__ out) {
-  const uint64_t shot = ((uint64_t)blockIdx.x * kThreads + threadIdx.x) >> 6;
-  const int lane = threadIdx.x & 63;
-  if (shot >= shots) return;  // whole waves leave together
+__device__ __forceinline__ double wave_inclusive(double x, int lane) {
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const double y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  return x;
+}
+
+// The chunk of every shot, one thread each: the first with incl > target (or,
+// past the end, the first reaching total).
+__global__ __launch_bounds__(kThreads) void k_find_chunks(const double* __restrict__ incl, uint64_t nchunks,
+                                                         const double* __restrict__ u, uint64_t shots,
+                                                         uint64_t* __restrict__ out) {
+  const uint64_t shot = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (shot >= shots) return;
   const double total = incl[nchunks - 1];
   if (!(total > 0.0)) {
-    if (lane == 0) out[shot] = kNoSample;
+    out[shot] = kNoSample;
     return;
   }
-  double target = u[shot] * total;
+  const double target = u[shot] * total;
   const bool past_end = !(target < total);
-  // first chunk with incl > target (or, past the end, the first reaching total)
   uint64_t lo = 0, hi = nchunks - 1;
   while (lo < hi) {
     const uint64_t mid = lo + (hi - lo) / 2;
@@ -477,26 +499,74 @@ __global__ __launch_bounds__(kThreads) void k_sample(const float2* __restrict__ 
     if (go_left) hi = mid;
     else lo = mid + 1;
   }
-  const uint64_t ch = lo;
-  const double r = (past_end ? total : target) - (ch > 0 ? incl[ch - 1] : 0.0);
-  const uint64_t len = (uint64_t)1 << cbits;
-  const uint64_t base = ch << cbits;
+  out[shot] = lo;
+}
+
+// in: out[shot] is the shot's chunk; out: the amplitude it picks in it
+__global__ __launch_bounds__(kThreads) void k_sample(const float2* __restrict__ psi, int cbits, int bbits,
+                                                    const double* __restrict__ incl, const double* __restrict__ parts,
+                                                    uint64_t nchunks, const double* __restrict__ u, uint64_t shots,
+                                                    uint64_t* __restrict__ out) {
+  const uint64_t shot = ((uint64_t)blockIdx.x * kThreads + threadIdx.x) >> 6;
+  const int lane = threadIdx.x & 63;
+  if (shot >= shots) return;  // whole waves leave together
+  const uint64_t ch = out[shot];
+  if (ch == kNoSample) return;
+  const double total = incl[nchunks - 1];
+  const double target = u[shot] * total;
+  const bool past_end = !(target < total);
+  // what is left of the target inside the chunk; past the end nothing crosses
+  // and the last amplitude with p > 0 is taken
+  double r = target - (ch > 0 ? incl[ch - 1] : 0.0);
+  const int nparts = 1 << bbits;
+  double v = lane < nparts ? parts[(ch << bbits) + lane] : 0.0;
+  double x = wave_inclusive(v, lane);
+  uint64_t cross = __ballot(!past_end && x > r && v > 0.0);
+  uint64_t nz = __ballot(v > 0.0);
+  if (!nz) {
+    if (lane == 0) out[shot] = kNoSample;
+    return;
+  }
+  const bool last_part = !cross;
+  const int part = cross ? __ffsll((long long)cross) - 1 : 63 - __clzll(nz);
+  r -= __shfl(x - v, part, 64);
+  const uint64_t len = (uint64_t)1 << (cbits - bbits);
+  const uint64_t base = (ch << cbits) + (uint64_t)part * len;
   double acc = 0.0;
   uint64_t last_nz = kNoSample, found = kNoSample;
-  for (uint64_t s = 0; s < len && found == kNoSample; s += 64) {
-    const uint64_t i = s + lane;
-    const double v = i < len ? sq(psi[base + i]) : 0.0;
-    double x = v;
+  for (uint64_t s = 0; s < len && found == kNoSample; s += 512) {
+    double p[8];
+    v = 0.0;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const double y = __shfl_up(x, o, 64);
-      if (lane >= o) x += y;
+    for (int e = 0; e < 8; e += 2) {  // 16-byte loads; a part is whole elements
+      const uint64_t i = s + (uint64_t)lane * 8 + e;
+      const float4 a = i < len ? *reinterpret_cast<const float4*>(psi + base + i) : make_float4(0.f, 0.f, 0.f, 0.f);
+      p[e] = sq(make_float2(a.x, a.y));
+      p[e + 1] = sq(make_float2(a.z, a.w));
+      v += p[e];
+      v += p[e + 1];
     }
-    const uint64_t nz = __ballot(v > 0.0);
-    if (nz) last_nz = base + s + 63 - __clzll(nz);
-    if (!past_end) {
-      const uint64_t cross = __ballot(acc + x > r && v > 0.0);
-      if (cross) found = base + s + __ffsll((long long)cross) - 1;
+    x = wave_inclusive(v, lane);
+    cross = __ballot(!past_end && !last_part && acc + x > r && v > 0.0);
+    nz = __ballot(v > 0.0);
+    const int owner = cross ? __ffsll((long long)cross) - 1 : nz ? 63 - __clzll(nz) : -1;
+    if (owner >= 0) {
+      // the owner lane walks its eight amplitudes
+      const double before = acc + (x - v);
+      double run = 0.0;
+      int hit = -1, last = 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        run += p[e];
+        if (p[e] > 0.0) {
+          last = e;
+          if (hit < 0 && before + run > r) hit = e;
+        }
+      }
+      const int pick = __shfl(cross && hit >= 0 ? hit : last, owner, 64);
+      const uint64_t i = base + s + (uint64_t)owner * 8 + pick;
+      if (cross) found = i;
+      else last_nz = i;
     }
     acc += __shfl(x, 63, 64);
   }
@@ -626,9 +696,15 @@ int sample_chunk_bits(int n) {
   if (n - c > 22) c = n - 22;
   return c;
 }
+// Parts of a chunk, 2^b of at least 512 amplitudes: one load and scan finds
+// the part.
+int sample_part_bits(int n) {
+  const int c = sample_chunk_bits(n);
+  return c <= 9 ? 0 : c - 9 < 3 ? c - 9 : 3;
+}
 size_t sample_scratch_bytes(int n) {
   const uint64_t nchunks = (uint64_t)1 << (n - sample_chunk_bits(n));
-  return sizeof(double) * (nchunks + kMaxBlocks);
+  return sizeof(double) * (nchunks + kMaxBlocks + (nchunks << sample_part_bits(n)));
 }
 
 // prepare: build the chunk prefix sums in scratch (needed once per state);
@@ -639,16 +715,18 @@ void launch_sample(const void* psi, int n, bool prepare, const double* uniforms,
   const int c = sample_chunk_bits(n);
   if (c < 1) throw DeviceError{hipErrorInvalidValue, "k_sample: a chunk must hold whole 16-byte elements"};
   const uint64_t nchunks = (uint64_t)1 << (n - c);
+  const int b = sample_part_bits(n);
   double* incl = scratch;
   double* totals = scratch + nchunks;
+  double* parts = totals + kMaxBlocks;
   if (prepare) {
     const uint64_t waves_blocks = (nchunks * 64 + kThreads - 1) / kThreads;
     if (n >= kern::kNtMinQubits)
       hipLaunchKernelGGL(k_chunk_sums<true>, dim3((unsigned)waves_blocks), dim3(kThreads), 0, st,
-                         (const float2*)psi, c, nchunks, incl);
+                         (const float2*)psi, c, b, nchunks, incl, parts);
     else
       hipLaunchKernelGGL(k_chunk_sums<false>, dim3((unsigned)waves_blocks), dim3(kThreads), 0, st,
-                         (const float2*)psi, c, nchunks, incl);
+                         (const float2*)psi, c, b, nchunks, incl, parts);
     const uint64_t sblocks = (nchunks + kScanBlock - 1) / kScanBlock;
     if (sblocks > (uint64_t)kScanBlock) throw DeviceError{hipErrorInvalidValue, "k_sample: too many chunks"};
     hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)sblocks), dim3(kThreads), 0, st, incl, nchunks, totals);
@@ -659,9 +737,11 @@ void launch_sample(const void* psi, int n, bool prepare, const double* uniforms,
     }
   }
   if (shots) {
-    const uint64_t blocks = (shots * 64 + kThreads - 1) / kThreads;
-    hipLaunchKernelGGL(k_sample, dim3((unsigned)blocks), dim3(kThreads), 0, st, (const float2*)psi, c,
+    hipLaunchKernelGGL(k_find_chunks, dim3((unsigned)((shots + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
                        (const double*)incl, nchunks, uniforms, shots, out);
+    const uint64_t blocks = (shots * 64 + kThreads - 1) / kThreads;
+    hipLaunchKernelGGL(k_sample, dim3((unsigned)blocks), dim3(kThreads), 0, st, (const float2*)psi, c, b,
+                       (const double*)incl, (const double*)parts, nchunks, uniforms, shots, out);
   }
   SV_HIP(hipGetLastError());
 }
