@@ -26,8 +26,7 @@ struct sv_state {
   size_t ring_pos = 0;
   // reductions
   double* partials = nullptr;
-  double* norm_dev = nullptr;
-  double* norm_host = nullptr;  // pinned
+  double* norm_host = nullptr;  // pinned; the kernel writes it
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   hipEvent_t queued = nullptr;  // recorded after each launched chunk of passes
   // graph of the last use_graph call, with its own device copy of the pass
@@ -613,8 +612,7 @@ int sv_alloc(int n_qubits, int dtype, void* dev_buf, size_t buf_bytes, void* hip
   s->psi = dev_buf;
   s->stream = (hipStream_t)hip_stream;
   SV_HIP(hipGetDevice(&s->device));
-  SV_HIP(hipMalloc(&s->partials, sizeof(double) * (norm_partials_needed() + 1)));
-  s->norm_dev = s->partials + norm_partials_needed();
+  SV_HIP(hipMalloc(&s->partials, sizeof(double) * norm_partials_needed()));
   SV_HIP(hipHostMalloc(&s->norm_host, sizeof(double), hipHostMallocDefault));
   SV_HIP(hipEventCreate(&s->ev0));
   SV_HIP(hipEventCreate(&s->ev1));
@@ -742,8 +740,7 @@ int sv_apply_circuit(sv_state* s, const sv_gate* gates, size_t n_gates, const sv
   SV_HIP(hipSetDevice(s->device));
   if (o.precision == SV_PREC_FP16X3) {
     if (s->norm_known < 0.0) {  // measure it once (one read sweep)
-      launch_norm(s->psi, s->n, s->partials, norm_partials_needed(), s->norm_dev, s->stream);
-      SV_HIP(hipMemcpyAsync(s->norm_host, s->norm_dev, sizeof(double), hipMemcpyDeviceToHost, s->stream));
+      launch_norm(s->psi, s->n, s->partials, norm_partials_needed(), s->norm_host, s->stream);
       SV_HIP(hipStreamSynchronize(s->stream));
       s->norm_known = *s->norm_host;
     }
@@ -864,8 +861,7 @@ int sv_norm(sv_state* s, double* norm_sq) {
   if (!norm_sq) return fail(SV_EINVAL, "norm_sq is NULL");
   SV_GUARD_BEGIN
   SV_HIP(hipSetDevice(s->device));
-  launch_norm(s->psi, s->n, s->partials, norm_partials_needed(), s->norm_dev, s->stream);
-  SV_HIP(hipMemcpyAsync(s->norm_host, s->norm_dev, sizeof(double), hipMemcpyDeviceToHost, s->stream));
+  launch_norm(s->psi, s->n, s->partials, norm_partials_needed(), s->norm_host, s->stream);
   SV_HIP(hipStreamSynchronize(s->stream));
   *norm_sq = *s->norm_host;
   s->norm_known = *norm_sq;
@@ -928,30 +924,42 @@ int sv_expect_pauli(sv_state* s, size_t n_terms, const uint64_t* xmask, const ui
       }
     }
   }
-  const size_t outs = sizeof(double) * 16 * sweep_f.size();
-  meas_reserve(s, pauli_scratch_bytes() + outs, outs);
-  double* scratch = reinterpret_cast<double*>(s->meas_dev);
-  double* res = reinterpret_cast<double*>(s->meas_dev + pauli_scratch_bytes());
-  for (size_t w = 0; w < sweep_f.size(); ++w) {
-    uint64_t z[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (size_t j = 0; j < sweep_terms[w].size(); ++j) z[j] = zmask[sweep_terms[w][j]];
-    launch_pauli(s->psi, s->n, sweep_f[w], (int)sweep_terms[w].size(), z, scratch, res + 16 * w, s->stream);
-  }
-  SV_HIP(hipMemcpyAsync(s->meas_host, res, outs, hipMemcpyDeviceToHost, s->stream));
-  SV_HIP(hipStreamSynchronize(s->stream));
+  // the sums land in pinned host memory, written by the kernel itself
+  const size_t per_call = std::min(sweep_f.size(), kPauliSweepsMax);
+  meas_reserve(s, pauli_scratch_bytes(s->n, per_call), sizeof(double) * 8 * per_call);
   const double* h = reinterpret_cast<const double*>(s->meas_host);
-  for (size_t w = 0; w < sweep_f.size(); ++w)
-    for (size_t j = 0; j < sweep_terms[w].size(); ++j) {
-      const size_t t = sweep_terms[w][j];
-      const double re = h[16 * w + 2 * j], im = h[16 * w + 2 * j + 1];
-      // P = i^ny X^f Z^z with ny = |f & z| (the Y letters): Re(i^ny (re + i im))
-      switch (__builtin_popcountll(xmask[t] & zmask[t]) & 3) {
-        case 0: out[t] = re; break;
-        case 1: out[t] = -im; break;
-        case 2: out[t] = -re; break;
-        default: out[t] = im; break;
+  std::vector<PauliSweep> sweeps;
+  std::vector<int> order;
+  for (size_t w0 = 0; w0 < sweep_f.size(); w0 += per_call) {
+    sweeps.assign(std::min(per_call, sweep_f.size() - w0), PauliSweep{});
+    for (size_t w = 0; w < sweeps.size(); ++w) {
+      sweeps[w].f = sweep_f[w0 + w];
+      sweeps[w].terms = (int)sweep_terms[w0 + w].size();
+      for (int j = 0; j < sweeps[w].terms; ++j) sweeps[w].z[j] = zmask[sweep_terms[w0 + w][j]];
+    }
+    launch_pauli(s->psi, s->n, sweeps, order, reinterpret_cast<double*>(s->meas_dev),
+                 reinterpret_cast<double*>(s->meas_host), s->stream);
+    SV_HIP(hipStreamSynchronize(s->stream));
+    for (size_t i = 0; i < order.size(); ++i) {
+      const uint64_t f = sweeps[order[i]].f;
+      const std::vector<size_t>& terms = sweep_terms[w0 + order[i]];
+      for (size_t j = 0; j < terms.size(); ++j) {
+        const uint64_t z = zmask[terms[j]];
+        // sum_i (-1)^{|(i^f) & z|} conj(c_i) c_{i^f}: a pair's two terms add
+        // up to 2 Re w for an even |f & z| and -2i Im w for an odd one
+        const double v = f ? 2.0 * h[8 * i + j] : h[8 * i + j];
+        const bool odd = __builtin_popcountll(f & z) & 1;
+        const double re = odd ? 0.0 : v, im = odd ? -v : 0.0;
+        // P = i^ny X^f Z^z with ny = |f & z| (the Y letters): Re(i^ny (re + i im))
+        switch (__builtin_popcountll(f & z) & 3) {
+          case 0: out[terms[j]] = re; break;
+          case 1: out[terms[j]] = -im; break;
+          case 2: out[terms[j]] = -re; break;
+          default: out[terms[j]] = im; break;
+        }
       }
     }
+  }
   return SV_OK;
   SV_GUARD_END(s)
 }
@@ -971,10 +979,9 @@ int sv_marginal_probs(sv_state* s, int n_meas, const int32_t* qubits, double* ou
   SV_GUARD_BEGIN
   SV_HIP(hipSetDevice(s->device));
   const size_t outs = sizeof(double) << n_meas;
-  meas_reserve(s, marginal_scratch_bytes(n_meas) + outs, outs);
-  double* res = reinterpret_cast<double*>(s->meas_dev + marginal_scratch_bytes(n_meas));
-  launch_marginal(s->psi, s->n, n_meas, q, reinterpret_cast<double*>(s->meas_dev), res, s->stream);
-  SV_HIP(hipMemcpyAsync(s->meas_host, res, outs, hipMemcpyDeviceToHost, s->stream));
+  meas_reserve(s, marginal_scratch_bytes(n_meas), outs);
+  launch_marginal(s->psi, s->n, n_meas, q, reinterpret_cast<double*>(s->meas_dev),
+                  reinterpret_cast<double*>(s->meas_host), s->stream);  // written by the kernel itself
   SV_HIP(hipStreamSynchronize(s->stream));
   std::memcpy(out, s->meas_host, outs);
   return SV_OK;

@@ -4,6 +4,8 @@
 // sampling.  Every sum is in FP64 in a fixed order, so results do not vary
 // between runs; squares and products of complex64 amplitudes are formed in
 // FP64, where they are exact.
+#include <algorithm>
+
 #include "k_common.h"
 
 namespace sv {
@@ -147,9 +149,58 @@ __device__ __forceinline__ void block_partials(const double* acc, uint32_t own, 
 // (amplitudes 2x, 2x + 1); mode 2 items are quads: the element at i (bit h
 // clear, i even) and the element holding its partners i ^ f and
 // (i + 1) ^ f.  Every thread keeps two items in flight.
-template <bool NT, int MODE, int TERMS>
-__global__ __launch_bounds__(kThreads) void k_pauli_partial(const float4* __restrict__ psi, const PauliArgs a,
-                                                           double* __restrict__ partials) {
+// The sums of several sweeps of a state held in the caches, in one launch:
+// blockIdx.y is the sweep, and each thread walks its items as above.  A sweep
+// by itself is 4 to 8 us of launch and latency at 20 qubits whatever it reads,
+// so an Ising Hamiltonian's 24 sweeps in a launch each, with a column sum
+// behind every one, took 302 us; as three launches and a wait it takes 48.
+template <int TERMS>
+struct PauliSweeps {
+  static constexpr int kMax = 3072 / (8 + 8 * TERMS);  // sweeps in one launch's arguments
+  uint64_t f[kMax];
+  uint64_t z[kMax][TERMS];
+};
+
+// coefficients, masks and walk of one sweep (host and device)
+template <int TERMS>
+__host__ __device__ inline int pauli_args(PauliArgs& a, int n, uint64_t f, const uint64_t* z) {
+  a.f = f;
+  a.odd = 0;
+  const int mode = f > 1 ? 2 : (int)f;
+  a.lowmask = 0;
+  a.items = (uint64_t)1 << (n - 1);  // n = 1: one element
+  if (mode == 2) {
+    const int h = 63 - __builtin_clzll(f);  // h >= 1, so n >= 2
+    a.lowmask = ((uint64_t)1 << h) - 1;
+    a.items = (uint64_t)1 << (n - 2);
+  }
+  // mode 0 (|c_i|^2, |c_{i+1}|^2): the sign of z_t bit 0 on the second; modes
+  // 1, 2: Re w for an even |f & z_t|, Im w for an odd one, and in mode 2 the
+  // pair at i + 1 again signed by bit 0
+  constexpr uint32_t kOne = 0x3FF00000u, kNeg = 0x80000000u;
+#pragma unroll
+  for (int t = 0; t < TERMS; ++t) {
+    a.z[t] = z[t];
+    const bool im = __builtin_popcountll(f & z[t]) & 1;
+    a.odd |= (uint32_t)im << t;
+    const uint32_t zeta = (z[t] & 1) ? kNeg : 0u;
+    if (mode == 0) {
+      a.chi[t][0] = kOne;
+      a.chi[t][1] = kOne | zeta;
+      a.chi[t][2] = a.chi[t][3] = 0u;
+    } else {
+      a.chi[t][0] = im ? 0u : kOne;
+      a.chi[t][1] = im ? kOne : 0u;
+      a.chi[t][2] = a.chi[t][0] ? a.chi[t][0] | zeta : 0u;
+      a.chi[t][3] = a.chi[t][1] ? a.chi[t][1] | zeta : 0u;
+    }
+  }
+  return mode;
+}
+
+template <int MODE, int TERMS>
+__device__ __forceinline__ void pauli_walk(const float4* __restrict__ psi, const PauliArgs& a,
+                                           double* __restrict__ partials) {
   constexpr int NV = MODE == 2 ? 4 : 2;
   double acc[kTerms];
 #pragma unroll
@@ -170,12 +221,12 @@ __global__ __launch_bounds__(kThreads) void k_pauli_partial(const float4* __rest
       const bool has1 = m + 1 < M;
       const uint64_t im = first_amp<MODE>(a, m * nth);
       const uint64_t i0 = iT | im, i1 = has1 ? i0 | i_step : i0;
-      const float4 A0 = gld<NT>(psi + (i0 >> 1));
-      const float4 A1 = gld<NT>(psi + (i1 >> 1));
+      const float4 A0 = gld<false>(psi + (i0 >> 1));
+      const float4 A1 = gld<false>(psi + (i1 >> 1));
       float4 B0 = A0, B1 = A1;
       if (MODE == 2) {
-        B0 = gld<NT>(psi + (((i0 ^ a.f) & ~(uint64_t)1) >> 1));
-        B1 = gld<NT>(psi + (((i1 ^ a.f) & ~(uint64_t)1) >> 1));
+        B0 = gld<false>(psi + (((i0 ^ a.f) & ~(uint64_t)1) >> 1));
+        B1 = gld<false>(psi + (((i1 ^ a.f) & ~(uint64_t)1) >> 1));
       }
       const uint32_t sig = sign_bits(a, im, TERMS);
       double v[NV];
@@ -191,6 +242,18 @@ __global__ __launch_bounds__(kThreads) void k_pauli_partial(const float4* __rest
   }
   const uint32_t own = sign_bits(a, iT, TERMS) ^ (kFlips<MODE> ? last : 0u);
   block_partials(acc, own, partials);
+}
+
+template <int TERMS>
+__global__ __launch_bounds__(kThreads) void k_pauli_sweeps(const float4* __restrict__ psi, int n,
+                                                          const PauliSweeps<TERMS> s, int first,
+                                                          double* __restrict__ partials) {
+  PauliArgs a;
+  const int mode = pauli_args<TERMS>(a, n, s.f[blockIdx.y], s.z[blockIdx.y]);
+  double* out = partials + (size_t)(first + blockIdx.y) * gridDim.x * kTerms;
+  if (mode == 0) pauli_walk<0, TERMS>(psi, a, out);
+  else if (mode == 1) pauli_walk<1, TERMS>(psi, a, out);
+  else pauli_walk<2, TERMS>(psi, a, out);
 }
 
 // The same sums on a streamed state, walked the way the sampling chunk sums
@@ -245,15 +308,10 @@ __global__ __launch_bounds__(kThreads) void k_pauli_chunks(const float4* __restr
 // Column sums of the blocks x width matrix of per-block partials, in a fixed
 // order: workgroup g owns columns 64 g .. 64 g + 63 (one per lane); each of
 // its 16 waves sums a contiguous run of rows, and wave 0 then adds the 16
-// wave sums in wave order.  With PAULI the column sums S_t become
-// out[2t], out[2t + 1] = Re, Im of sum_i (-1)^{|(i^f) & z_t|} conj(c_i)
-// c_{i^f} (the i^ny factor is applied on the host); otherwise out[col] is
-// the sum itself.
+// wave sums in wave order.
 constexpr int kFinalWaves = 16;
-template <bool PAULI>
 __global__ __launch_bounds__(64 * kFinalWaves) void k_column_sums(const double* __restrict__ partials, int blocks,
-                                                                  int width, int mode, uint32_t odd,
-                                                                  double* __restrict__ out) {
+                                                                  int width, double* __restrict__ out) {
   __shared__ double part[kFinalWaves][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int col = blockIdx.x * 64 + lane;
@@ -269,14 +327,24 @@ __global__ __launch_bounds__(64 * kFinalWaves) void k_column_sums(const double* 
   if (w != 0 || col >= width) return;
   double t = 0.0;
   for (int x = 0; x < kFinalWaves; ++x) t += part[x][lane];
-  if (PAULI) {
-    const double scale = mode == 0 ? 1.0 : 2.0;
-    const bool is_odd = (odd >> col) & 1;
-    out[2 * col] = is_odd ? 0.0 : scale * t;
-    out[2 * col + 1] = is_odd ? -scale * t : 0.0;
-  } else {
-    out[col] = t;
-  }
+  out[col] = t;
+}
+
+// The Pauli sums of every sweep: workgroup s adds the blocks x kTerms partials
+// of sweep s, 32 rows at a time, in a fixed order.
+__global__ __launch_bounds__(kThreads) void k_pauli_final(const double* __restrict__ partials, int blocks,
+                                                         double* __restrict__ out) {
+  __shared__ double part[kThreads];
+  const double* p = partials + (size_t)blockIdx.x * blocks * kTerms;
+  double s = 0.0;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < blocks * kTerms; i += kThreads) s += p[i];
+  part[threadIdx.x] = s;
+  __syncthreads();
+  if (threadIdx.x >= kTerms) return;
+  double t = 0.0;
+  for (int r = threadIdx.x; r < kThreads; r += kTerms) t += part[r];
+  out[(size_t)blockIdx.x * kTerms + threadIdx.x] = t;
 }
 
 // ------------------------------------------------------- marginal probabilities
@@ -581,79 +649,74 @@ unsigned blocks_for(uint64_t items, uint64_t per_thread) {
 
 }  // namespace
 
-size_t pauli_scratch_bytes() { return sizeof(double) * ((size_t)kMaxBlocks + 1) * 2 * kTerms; }
-
-// out: 2 * kTerms doubles (device).  scratch: pauli_scratch_bytes().
-void launch_pauli(const void* psi, int n, uint64_t f, int nt, const uint64_t* z, double* scratch, double* out,
-                  hipStream_t st) {
-  if (nt < 1 || nt > kTerms) throw DeviceError{hipErrorInvalidValue, "k_pauli: 1..8 terms per sweep"};
-  PauliArgs a{};
-  a.f = f;
-  for (int t = 0; t < nt; ++t) {
-    a.z[t] = z[t];
-    if (__builtin_popcountll(f & z[t]) & 1) a.odd |= 1u << t;
-  }
-  if (n < 1 || (n < 64 && (f >> n) != 0)) throw DeviceError{hipErrorInvalidValue, "k_pauli: flip mask past n"};
-  int mode;
-  if (f == 0 || f == 1) {
-    mode = (int)f;
-    a.items = (uint64_t)1 << (n - 1);  // n = 1: one element
-  } else {
-    const int h = 63 - __builtin_clzll(f);  // h >= 1, so n >= 2
-    mode = 2;
-    a.lowmask = ((uint64_t)1 << h) - 1;
-    a.items = (uint64_t)1 << (n - 2);
-  }
-  // coefficients of the item values: mode 0 (|c_i|^2, |c_{i+1}|^2) with the
-  // sign of z_t bit 0 on the second; modes 1, 2: Re w for an even |f & z_t|,
-  // Im w for an odd one, and in mode 2 the pair at i + 1 again signed by bit 0
-  constexpr uint32_t kOne = 0x3FF00000u, kNeg = 0x80000000u;
-  for (int t = 0; t < nt; ++t) {
-    const uint32_t zeta = (z[t] & 1) ? kNeg : 0u;
-    const bool im = (a.odd >> t) & 1;
-    if (mode == 0) {
-      a.chi[t][0] = kOne;
-      a.chi[t][1] = kOne | zeta;
-    } else {
-      a.chi[t][0] = im ? 0u : kOne;
-      a.chi[t][1] = im ? kOne : 0u;
-      a.chi[t][2] = a.chi[t][0] ? a.chi[t][0] | zeta : 0u;
-      a.chi[t][3] = a.chi[t][1] ? a.chi[t][1] | zeta : 0u;
+namespace {
+// one class of sweeps (all of at most TERMS terms): partials of sweep i at
+// (first + i) * blocks * kTerms
+template <int TERMS>
+void pauli_class(const void* psi, int n, const std::vector<PauliSweep>& sweeps, const std::vector<int>& which,
+                 int first, unsigned blocks, double* partials, hipStream_t st) {
+  if (n >= kern::kNtMinQubits) {  // streamed: a launch per sweep, each bound by memory
+    for (size_t i = 0; i < which.size(); ++i) {
+      PauliArgs a{};
+      const int mode = pauli_args<TERMS>(a, n, sweeps[which[i]].f, sweeps[which[i]].z);
+      auto* kernel = mode == 0 ? k_pauli_chunks<0, TERMS> : mode == 1 ? k_pauli_chunks<1, TERMS> : k_pauli_chunks<2, TERMS>;
+      hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, st, (const float4*)psi, a,
+                         partials + (first + i) * blocks * kTerms);
     }
+    return;
   }
-  const unsigned blocks = blocks_for(a.items, 2);  // a power of two, as the kernel's split of signs needs
-  const int terms = nt <= 1 ? 1 : nt <= 2 ? 2 : nt <= 4 ? 4 : 8;
-  const bool nt_loads = n >= kern::kNtMinQubits;
-  using Kern = void (*)(const float4*, PauliArgs, double*);
-  static constexpr Kern table[2][3][4] = {
-      {{k_pauli_partial<false, 0, 1>, k_pauli_partial<false, 0, 2>, k_pauli_partial<false, 0, 4>,
-        k_pauli_partial<false, 0, 8>},
-       {k_pauli_partial<false, 1, 1>, k_pauli_partial<false, 1, 2>, k_pauli_partial<false, 1, 4>,
-        k_pauli_partial<false, 1, 8>},
-       {k_pauli_partial<false, 2, 1>, k_pauli_partial<false, 2, 2>, k_pauli_partial<false, 2, 4>,
-        k_pauli_partial<false, 2, 8>}},
-      {{k_pauli_partial<true, 0, 1>, k_pauli_partial<true, 0, 2>, k_pauli_partial<true, 0, 4>,
-        k_pauli_partial<true, 0, 8>},
-       {k_pauli_partial<true, 1, 1>, k_pauli_partial<true, 1, 2>, k_pauli_partial<true, 1, 4>,
-        k_pauli_partial<true, 1, 8>},
-       {k_pauli_partial<true, 2, 1>, k_pauli_partial<true, 2, 2>, k_pauli_partial<true, 2, 4>,
-        k_pauli_partial<true, 2, 8>}}};
-  const int ti = terms == 1 ? 0 : terms == 2 ? 1 : terms == 4 ? 2 : 3;
-  unsigned used = blocks;
-  const uint64_t chunk_waves = (uint64_t)kMaxBlocks * (kThreads / 64);
-  if (nt_loads && a.items % (chunk_waves * kChunkItems) == 0) {
-    static constexpr Kern chunks[3][4] = {
-        {k_pauli_chunks<0, 1>, k_pauli_chunks<0, 2>, k_pauli_chunks<0, 4>, k_pauli_chunks<0, 8>},
-        {k_pauli_chunks<1, 1>, k_pauli_chunks<1, 2>, k_pauli_chunks<1, 4>, k_pauli_chunks<1, 8>},
-        {k_pauli_chunks<2, 1>, k_pauli_chunks<2, 2>, k_pauli_chunks<2, 4>, k_pauli_chunks<2, 8>}};
-    used = kMaxBlocks;
-    hipLaunchKernelGGL(chunks[mode][ti], dim3(used), dim3(kThreads), 0, st, (const float4*)psi, a, scratch);
-  } else {
-    hipLaunchKernelGGL(table[nt_loads][mode][ti], dim3(blocks), dim3(kThreads), 0, st, (const float4*)psi, a,
-                       scratch);
+  for (size_t i0 = 0; i0 < which.size(); i0 += PauliSweeps<TERMS>::kMax) {
+    PauliSweeps<TERMS> s;
+    const size_t m = std::min(which.size() - i0, (size_t)PauliSweeps<TERMS>::kMax);
+    for (size_t i = 0; i < m; ++i) {
+      s.f[i] = sweeps[which[i0 + i]].f;
+      std::copy(sweeps[which[i0 + i]].z, sweeps[which[i0 + i]].z + TERMS, s.z[i]);
+    }
+    hipLaunchKernelGGL(k_pauli_sweeps<TERMS>, dim3(blocks, (unsigned)m), dim3(kThreads), 0, st, (const float4*)psi, n,
+                       s, first + (int)i0, partials);
   }
-  hipLaunchKernelGGL(k_column_sums<true>, dim3(1), dim3(64 * kFinalWaves), 0, st, (const double*)scratch,
-                     (int)used, kTerms, mode, a.odd, out);
+}
+}  // namespace
+
+// Workgroups per sweep.  Streamed states: all that are resident, each wave
+// walking whole chunks.  Cached ones: a power of two (the kernel's split of
+// signs needs it) of at least two items a thread and about 4096 in a launch.
+unsigned pauli_blocks(int n, size_t sweeps) {
+  if (n >= kern::kNtMinQubits) return kMaxBlocks;
+  unsigned b = 1;
+  const uint64_t items = n > 1 ? (uint64_t)1 << (n - 2) : 1;
+  while (b < (unsigned)kMaxBlocks && (uint64_t)b * 4 * kThreads <= items && b * 2 * sweeps <= 4096) b *= 2;
+  return b;
+}
+size_t pauli_scratch_bytes(int n, size_t sweeps) {
+  return sizeof(double) * kTerms * sweeps * pauli_blocks(n, sweeps);
+}
+
+// Sums of every sweep: out[8 w + t] = sum over pairs (or amplitudes) of term t
+// of sweep order[w].  `order` receives the sweeps' order.
+void launch_pauli(const void* psi, int n, const std::vector<PauliSweep>& sweeps, std::vector<int>& order,
+                  double* scratch, double* out, hipStream_t st) {
+  const unsigned blocks = pauli_blocks(n, sweeps.size());
+  if (n < 1) throw DeviceError{hipErrorInvalidValue, "k_pauli: n"};
+  std::vector<int> cls[4];
+  for (size_t w = 0; w < sweeps.size(); ++w) {
+    const PauliSweep& s = sweeps[w];
+    if (s.terms < 1 || s.terms > kTerms) throw DeviceError{hipErrorInvalidValue, "k_pauli: 1..8 terms per sweep"};
+    if (n < 64 && (s.f >> n) != 0) throw DeviceError{hipErrorInvalidValue, "k_pauli: flip mask past n"};
+    cls[s.terms <= 1 ? 0 : s.terms <= 2 ? 1 : s.terms <= 4 ? 2 : 3].push_back((int)w);
+  }
+  order.clear();
+  int first = 0;
+  for (int c = 0; c < 4; ++c) {
+    if (c == 0) pauli_class<1>(psi, n, sweeps, cls[c], first, blocks, scratch, st);
+    else if (c == 1) pauli_class<2>(psi, n, sweeps, cls[c], first, blocks, scratch, st);
+    else if (c == 2) pauli_class<4>(psi, n, sweeps, cls[c], first, blocks, scratch, st);
+    else pauli_class<8>(psi, n, sweeps, cls[c], first, blocks, scratch, st);
+    order.insert(order.end(), cls[c].begin(), cls[c].end());
+    first += (int)cls[c].size();
+  }
+  hipLaunchKernelGGL(k_pauli_final, dim3((unsigned)sweeps.size()), dim3(kThreads), 0, st, (const double*)scratch,
+                     (int)blocks, out);
   SV_HIP(hipGetLastError());
 }
 
@@ -684,8 +747,8 @@ void launch_marginal(const void* psi, int n, int m, const int* qubits, double* s
   else
     hipLaunchKernelGGL(k_marginal_partial<false>, dim3(blocks), dim3(kThreads), sizeof(double) * 4 * M, st,
                        (const float2*)psi, a, scratch);
-  hipLaunchKernelGGL(k_column_sums<false>, dim3((M + 63) / 64), dim3(64 * kFinalWaves), 0, st,
-                     (const double*)scratch, (int)blocks, M, 0, 0u, out);
+  hipLaunchKernelGGL(k_column_sums, dim3((M + 63) / 64), dim3(64 * kFinalWaves), 0, st, (const double*)scratch,
+                     (int)blocks, M, out);
   SV_HIP(hipGetLastError());
 }
 

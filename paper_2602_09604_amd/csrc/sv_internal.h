@@ -212,9 +212,16 @@ bool shfl_eligible(int n, int k, const int* s);
 void launch_shfl(const Pass& p, int n, void* psi, const float2* U, hipStream_t st);
 
 // State reads (k_measure.hip).
-size_t pauli_scratch_bytes();
-void launch_pauli(const void* psi, int n, uint64_t f, int nt, const uint64_t* z, double* scratch, double* out,
-                  hipStream_t st);
+// One sweep of the Pauli sums: up to eight terms that share a flip mask.
+struct PauliSweep {
+  uint64_t f = 0;
+  int terms = 0;
+  uint64_t z[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+};
+constexpr size_t kPauliSweepsMax = 256;  // sweeps per call of launch_pauli
+size_t pauli_scratch_bytes(int n, size_t sweeps);
+void launch_pauli(const void* psi, int n, const std::vector<PauliSweep>& sweeps, std::vector<int>& order,
+                  double* scratch, double* out, hipStream_t st);
 int marginal_max_qubits();
 size_t marginal_scratch_bytes(int m);
 void launch_marginal(const void* psi, int n, int m, const int* qubits, double* scratch, double* out,
