@@ -299,6 +299,12 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
   if (passes.empty()) return;
   const bool timing = o.timing && stats;
   const bool graph = o.use_graph && !timing;
+  if (passes.size() == 1 && !stats && !graph && pass_by_value(s->n, passes[0])) {
+    PassValue u;
+    encode_pass_data(passes[0], mats[0], u.v);
+    launch_pass_value(passes[0], s->n, s->psi, u, s->stream);
+    return;
+  }
   // Consecutive passes that fit in one tile go out as one sweep; a timed call
   // and one with a forced variant launch every pass by itself.
   std::vector<Launch> launches;

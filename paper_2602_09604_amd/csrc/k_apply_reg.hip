@@ -20,9 +20,7 @@ struct RegArgs {
 //   and 2l'+1; K = k-1 element-space targets at s[j]-1 for j >= 1.
 // MODE 2 (ONE):  float2 elements, one group per lane, K = k targets at s[j].
 template <int K, int MODE, typename IDX, bool NT>
-__global__ __launch_bounds__(256) void k_apply_reg(void* __restrict__ psi_,
-                                                   const float2* __restrict__ U,
-                                                   const RegArgs<IDX> a) {
+__device__ __forceinline__ void reg_pass(void* __restrict__ psi_, const float2* __restrict__ U, const RegArgs<IDX>& a) {
   constexpr int D = 1 << K;  // loads per lane
   const IDX g = ((IDX)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
   if (g >= a.groups) return;
@@ -60,6 +58,20 @@ __global__ __launch_bounds__(256) void k_apply_reg(void* __restrict__ psi_,
         gst<NT>(psi + base + local_offset<K, IDX>(r, a.stride), pair_row<K, MODE>(v, U, r));
     }
   }
+}
+
+template <int K, int MODE, typename IDX, bool NT>
+__global__ __launch_bounds__(256) void k_apply_reg(void* __restrict__ psi, const float2* __restrict__ U,
+                                                   const RegArgs<IDX> a) {
+  reg_pass<K, MODE, IDX, NT>(psi, U, a);
+}
+
+// The same with the pass data in the kernel's arguments (PassValue): nothing
+// is uploaded, so the launch waits for no copy.
+template <int K, int MODE>
+__global__ __launch_bounds__(256) void k_apply_reg_value(void* __restrict__ psi, const PassValue u,
+                                                         const RegArgs<uint32_t> a) {
+  reg_pass<K, MODE, uint32_t, false>(psi, reinterpret_cast<const float2*>(u.v), a);
 }
 
 // MODE 0 / 1 with targets on element bits 0..2 (set TM; amplitude bits 1..3)
@@ -190,10 +202,9 @@ bool reg_streams(int n, int k, const int* s) { return reg_exchange_mask(n, k, s)
 
 namespace {
 
-template <typename IDX, bool NT>
-void launch_reg(const Pass& p, int n, void* psi, const float2* U, hipStream_t st) {
+template <typename IDX>
+RegArgs<IDX> reg_args(const Pass& p, int n, int& mode, int& K) {
   RegArgs<IDX> a{};
-  int mode, K;
   int pos[SV_MAX_K];
   if (p.s[0] == 0) {           // bit 0 is a target: it lives inside the float4
     mode = 1;
@@ -215,6 +226,13 @@ void launch_reg(const Pass& p, int n, void* psi, const float2* U, hipStream_t st
     a.lowmask[j] = ((IDX)1 << pos[j]) - 1;
     a.stride[j] = (IDX)1 << pos[j];
   }
+  return a;
+}
+
+template <typename IDX, bool NT>
+void launch_reg(const Pass& p, int n, void* psi, const float2* U, hipStream_t st) {
+  int mode, K;
+  const RegArgs<IDX> a = reg_args<IDX>(p, n, mode, K);
   if (mode == 0) launch_reg_k<IDX, NT, 0>(K, psi, U, a, st);
   else if (mode == 1) launch_reg_k<IDX, NT, 1>(K, psi, U, a, st);
   else launch_reg_k<IDX, NT, 2>(K, psi, U, a, st);
@@ -264,6 +282,44 @@ void launch_pass(const Pass& p, int n, void* psi, const unsigned char* data, hip
     } else {
       if (nt) launch_reg<uint64_t, true>(p, n, psi, U, st);
       else launch_reg<uint64_t, false>(p, n, psi, U, st);
+    }
+  }
+  SV_HIP(hipGetLastError());
+}
+
+namespace {
+template <int K, int MODE>
+void launch_value_t(void* psi, const PassValue& u, const RegArgs<uint32_t>& a, hipStream_t st) {
+  hipLaunchKernelGGL((k_apply_reg_value<K, MODE>), dim3((a.groups + 255) / 256), dim3(256), 0, st, psi, u, a);
+}
+}  // namespace
+
+// Passes whose data goes with the launch: up to three targets on a state held
+// in the caches, by the register, shuffle or controlled kernel.  Uploading 80
+// to 1280 bytes put a copy of about 6 us in front of a 3 us kernel; on a
+// streamed state it is lost in the pass.
+bool pass_by_value(int n, const Pass& p) {
+  return p.k <= 3 && n < kern::kNtMinQubits && p.mat_bytes <= sizeof(PassValue) &&
+         (p.variant == V_SHFL || p.variant == V_REG);
+}
+
+void launch_pass_value(const Pass& p, int n, void* psi, const PassValue& u, hipStream_t st) {
+  if (!pass_by_value(n, p)) throw DeviceError{hipErrorInvalidValue, "launch_pass_value: not such a pass"};
+  if (p.cmask) {
+    launch_ctrl_value(p, n, psi, u, st);
+  } else if (p.variant == V_SHFL) {
+    launch_shfl_value(p, n, psi, u, st);
+  } else {
+    int mode, K;
+    const RegArgs<uint32_t> a = reg_args<uint32_t>(p, n, mode, K);
+    switch (mode * 4 + K) {
+      case 1: launch_value_t<1, 0>(psi, u, a, st); break;
+      case 2: launch_value_t<2, 0>(psi, u, a, st); break;
+      case 3: launch_value_t<3, 0>(psi, u, a, st); break;
+      case 4: launch_value_t<0, 1>(psi, u, a, st); break;
+      case 5: launch_value_t<1, 1>(psi, u, a, st); break;
+      case 6: launch_value_t<2, 1>(psi, u, a, st); break;
+      default: throw DeviceError{hipErrorInvalidValue, "launch_pass_value: unsupported K/mode"};
     }
   }
   SV_HIP(hipGetLastError());

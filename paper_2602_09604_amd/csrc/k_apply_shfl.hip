@@ -38,8 +38,7 @@ __device__ __forceinline__ void cmac2(float2& acc, const float2 u, float vx, flo
 // 0 in .xy, 1 in .zw); with BIT0 it carries local indices 2 li and 2 li + 1
 // of one group.
 template <int KL, bool BIT0, bool NT>
-__global__ __launch_bounds__(256) void k_apply_shfl(float4* __restrict__ psi, const float2* __restrict__ U,
-                                                    const ShflArgs a) {
+__device__ __forceinline__ void shfl_pass(float4* __restrict__ psi, const float2* __restrict__ U, const ShflArgs& a) {
   constexpr int DL = 1 << KL;
   constexpr int D = DL << (BIT0 ? 1 : 0);  // matrix dimension
   const uint64_t e = ((uint64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
@@ -74,17 +73,32 @@ __global__ __launch_bounds__(256) void k_apply_shfl(float4* __restrict__ psi, co
 }
 
 template <int KL, bool BIT0, bool NT>
-void launch_t(float4* psi, const float2* U, const ShflArgs& a, uint64_t elems, hipStream_t st) {
-  const uint64_t blocks = elems / 256;
+__global__ __launch_bounds__(256) void k_apply_shfl(float4* __restrict__ psi, const float2* __restrict__ U,
+                                                    const ShflArgs a) {
+  shfl_pass<KL, BIT0, NT>(psi, U, a);
+}
+
+// the pass data in the kernel's arguments (see pass_by_value)
+template <int KL, bool BIT0>
+__global__ __launch_bounds__(256) void k_apply_shfl_value(float4* __restrict__ psi, const PassValue u,
+                                                          const ShflArgs a) {
+  shfl_pass<KL, BIT0, false>(psi, reinterpret_cast<const float2*>(u.v), a);
+}
+
+dim3 shfl_grid(int n) {
+  const uint64_t blocks = ((uint64_t)1 << (n - 1)) / 256;  // n >= 9
   const uint64_t gx = blocks < 65536 ? blocks : 65536;
-  const uint64_t gy = blocks / gx;  // elems is a power of two >= 256
-  hipLaunchKernelGGL((k_apply_shfl<KL, BIT0, NT>), dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, st, psi, U, a);
+  return dim3((unsigned)gx, (unsigned)(blocks / gx));
 }
 
 template <int KL, bool BIT0>
-void launch_kl(float4* psi, const float2* U, const ShflArgs& a, uint64_t elems, bool nt, hipStream_t st) {
-  if (nt) launch_t<KL, BIT0, true>(psi, U, a, elems, st);
-  else launch_t<KL, BIT0, false>(psi, U, a, elems, st);
+void launch_kl(float4* psi, const float2* U, const PassValue* value, const ShflArgs& a, int n, hipStream_t st) {
+  if (value) {
+    hipLaunchKernelGGL((k_apply_shfl_value<KL, BIT0>), shfl_grid(n), dim3(256), 0, st, psi, *value, a);
+    return;
+  }
+  auto* kernel = n >= kern::kNtMinQubits ? k_apply_shfl<KL, BIT0, true> : k_apply_shfl<KL, BIT0, false>;
+  hipLaunchKernelGGL(kernel, shfl_grid(n), dim3(256), 0, st, psi, U, a);
 }
 
 }  // namespace
@@ -105,24 +119,30 @@ bool shfl_eligible(int n, int k, const int* s) {
 }
 
 // The planner has checked shfl_eligible (targets sorted ascending).
-void launch_shfl(const Pass& p, int n, void* psi_, const float2* U, hipStream_t st) {
+static void launch_shfl_any(const Pass& p, int n, void* psi_, const float2* U, const PassValue* value, hipStream_t st) {
   if (!shfl_eligible(n, p.k, p.s)) throw DeviceError{hipErrorInvalidValue, "k_apply_shfl: targets not eligible"};
   ShflArgs a{};
   const bool bit0 = p.s[0] == 0;
   const int kl = p.k - (bit0 ? 1 : 0);
   for (int j = 0; j < kl; ++j) a.m[j] = 1 << (p.s[j + (bit0 ? 1 : 0)] - 1);
   float4* psi = reinterpret_cast<float4*>(psi_);
-  const uint64_t elems = (uint64_t)1 << (n - 1);
-  const bool nt = n >= kern::kNtMinQubits;
   switch (kl * 2 + (bit0 ? 1 : 0)) {
-    case 2: launch_kl<1, false>(psi, U, a, elems, nt, st); break;
-    case 3: launch_kl<1, true>(psi, U, a, elems, nt, st); break;
-    case 4: launch_kl<2, false>(psi, U, a, elems, nt, st); break;
-    case 5: launch_kl<2, true>(psi, U, a, elems, nt, st); break;
-    case 6: launch_kl<3, false>(psi, U, a, elems, nt, st); break;
+    case 2: launch_kl<1, false>(psi, U, value, a, n, st); break;
+    case 3: launch_kl<1, true>(psi, U, value, a, n, st); break;
+    case 4: launch_kl<2, false>(psi, U, value, a, n, st); break;
+    case 5: launch_kl<2, true>(psi, U, value, a, n, st); break;
+    case 6: launch_kl<3, false>(psi, U, value, a, n, st); break;
     default: throw DeviceError{hipErrorInvalidValue, "k_apply_shfl: lane targets"};
   }
   SV_HIP(hipGetLastError());
+}
+
+void launch_shfl(const Pass& p, int n, void* psi, const float2* U, hipStream_t st) {
+  launch_shfl_any(p, n, psi, U, nullptr, st);
+}
+
+void launch_shfl_value(const Pass& p, int n, void* psi, const PassValue& u, hipStream_t st) {
+  launch_shfl_any(p, n, psi, nullptr, &u, st);
 }
 
 }  // namespace sv

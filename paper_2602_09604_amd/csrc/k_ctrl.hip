@@ -22,8 +22,7 @@ struct CtrlArgs {
 };
 
 template <int K>
-__global__ __launch_bounds__(256) void k_apply_ctrl(float2* __restrict__ psi, const float2* __restrict__ U,
-                                                    const CtrlArgs a) {
+__device__ __forceinline__ void ctrl_pass(float2* __restrict__ psi, const float2* __restrict__ U, const CtrlArgs& a) {
   constexpr int D = 1 << K;
   const uint64_t t = ((uint64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
   if (t >= a.groups) return;
@@ -46,18 +45,37 @@ __global__ __launch_bounds__(256) void k_apply_ctrl(float2* __restrict__ psi, co
 }
 
 template <int K>
-void launch_ctrl_t(float2* psi, const float2* U, const CtrlArgs& a, hipStream_t st) {
+__global__ __launch_bounds__(256) void k_apply_ctrl(float2* __restrict__ psi, const float2* __restrict__ U,
+                                                    const CtrlArgs a) {
+  ctrl_pass<K>(psi, U, a);
+}
+
+// the pass data in the kernel's arguments (see pass_by_value)
+template <int K>
+__global__ __launch_bounds__(256) void k_apply_ctrl_value(float2* __restrict__ psi, const PassValue u,
+                                                          const CtrlArgs a) {
+  ctrl_pass<K>(psi, reinterpret_cast<const float2*>(u.v), a);
+}
+
+template <int K>
+void launch_ctrl_t(float2* psi, const float2* U, const PassValue* value, const CtrlArgs& a, hipStream_t st) {
   const uint64_t blocks = (a.groups + 255) / 256;
   const uint64_t gx = blocks < 65536 ? blocks : 65536;
-  const uint64_t gy = (blocks + gx - 1) / gx;
-  hipLaunchKernelGGL(k_apply_ctrl<K>, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, st, psi, U, a);
+  const dim3 grid((unsigned)gx, (unsigned)((blocks + gx - 1) / gx));
+  if constexpr (K <= 3) {
+    if (value) {
+      hipLaunchKernelGGL(k_apply_ctrl_value<K>, grid, dim3(256), 0, st, psi, *value, a);
+      return;
+    }
+  }
+  hipLaunchKernelGGL(k_apply_ctrl<K>, grid, dim3(256), 0, st, psi, U, a);
 }
 
 }  // namespace
 
 // The planner has checked: targets sorted, distinct and < n; controls < n,
 // disjoint from the targets; cval within cmask; k + c <= n.
-void launch_ctrl(const Pass& p, int n, void* psi_, const float2* U, hipStream_t st) {
+static void launch_ctrl_any(const Pass& p, int n, void* psi_, const float2* U, const PassValue* value, hipStream_t st) {
   CtrlArgs a{};
   a.fixed = p.cmask;
   for (int j = 0; j < p.k; ++j) {
@@ -72,14 +90,22 @@ void launch_ctrl(const Pass& p, int n, void* psi_, const float2* U, hipStream_t 
   a.groups = (uint64_t)1 << free_bits;
   float2* psi = reinterpret_cast<float2*>(psi_);
   switch (p.k) {
-    case 1: launch_ctrl_t<1>(psi, U, a, st); break;
-    case 2: launch_ctrl_t<2>(psi, U, a, st); break;
-    case 3: launch_ctrl_t<3>(psi, U, a, st); break;
-    case 4: launch_ctrl_t<4>(psi, U, a, st); break;
-    case 5: launch_ctrl_t<5>(psi, U, a, st); break;
-    case 6: launch_ctrl_t<6>(psi, U, a, st); break;
+    case 1: launch_ctrl_t<1>(psi, U, value, a, st); break;
+    case 2: launch_ctrl_t<2>(psi, U, value, a, st); break;
+    case 3: launch_ctrl_t<3>(psi, U, value, a, st); break;
+    case 4: launch_ctrl_t<4>(psi, U, value, a, st); break;
+    case 5: launch_ctrl_t<5>(psi, U, value, a, st); break;
+    case 6: launch_ctrl_t<6>(psi, U, value, a, st); break;
     default: throw DeviceError{hipErrorInvalidValue, "k_apply_ctrl: k outside 1..6"};
   }
+}
+
+void launch_ctrl(const Pass& p, int n, void* psi, const float2* U, hipStream_t st) {
+  launch_ctrl_any(p, n, psi, U, nullptr, st);
+}
+
+void launch_ctrl_value(const Pass& p, int n, void* psi, const PassValue& u, hipStream_t st) {
+  launch_ctrl_any(p, n, psi, nullptr, &u, st);
 }
 
 }  // namespace sv

@@ -84,6 +84,12 @@ struct Shape {
 
 // Kernel launchers (k_apply.hip, k_mfma.hip, k_state.hip).
 void launch_pass(const Pass& p, int n, void* psi, const unsigned char* data, hipStream_t st);  // data: the pass's own
+// A pass's data by value, as a kernel argument (k <= 3: complex64 and 3M copy).
+struct alignas(16) PassValue {
+  unsigned char v[1280];
+};
+bool pass_by_value(int n, const Pass& p);
+void launch_pass_value(const Pass& p, int n, void* psi, const PassValue& u, hipStream_t st);
 void launch_init_basis(void* psi, int n, uint64_t index, hipStream_t st);
 void launch_norm(const void* psi, int n, double* partials, int max_parts, double* out, hipStream_t st);
 int norm_partials_needed();
@@ -208,8 +214,10 @@ inline size_t phase_data_bytes(int n) { return kPhaseCoefBytes + 32 * ((size_t)1
 void phase_data(const PhasePoly& p, int n, unsigned char* out);
 void launch_phase(int n, void* psi, const unsigned char* data, hipStream_t st);
 void launch_ctrl(const Pass& p, int n, void* psi, const float2* U, hipStream_t st);
+void launch_ctrl_value(const Pass& p, int n, void* psi, const PassValue& u, hipStream_t st);
 bool shfl_eligible(int n, int k, const int* s);
 void launch_shfl(const Pass& p, int n, void* psi, const float2* U, hipStream_t st);
+void launch_shfl_value(const Pass& p, int n, void* psi, const PassValue& u, hipStream_t st);
 
 // State reads (k_measure.hip).
 // One sweep of the Pauli sums: up to eight terms that share a flip mask.
