@@ -562,22 +562,35 @@ using namespace sv;
 // state with sum |c|^2 <= 15 is safe, and unitary passes keep that sum.
 static constexpr double kFp16x3MaxNormSq = 15.0;
 
-// Every gate unitary to 1e-6 per entry of U^dagger U - I (FP64, host).
+// Every gate unitary to 1e-6 per entry of U^dagger U - I (FP64, host).  The
+// sums run row by row of U over contiguous columns, so that they vectorise.
 static bool gates_unitary(const sv_gate* g, size_t n) {
+  constexpr int kD = 1 << SV_MAX_K;
+  double mr[kD], mi[kD];                                // one row of U
+  static thread_local double gr[kD * kD], gi[kD * kD];  // upper triangle of U^dagger U, by rows
   for (size_t i = 0; i < n; ++i) {
     const int d = 1 << g[i].k;
     const double* m = g[i].matrix;
-    for (int a = 0; a < d; ++a)
-      for (int b = a; b < d; ++b) {
-        double re = 0.0, im = 0.0;  // (U^dagger U)[a][b] = sum_r conj(U[r][a]) U[r][b]
-        for (int r = 0; r < d; ++r) {
-          const double ar = m[2 * (r * d + a)], ai = m[2 * (r * d + a) + 1];
-          const double br = m[2 * (r * d + b)], bi = m[2 * (r * d + b) + 1];
-          re += ar * br + ai * bi;
-          im += ar * bi - ai * br;
-        }
-        if (std::fabs(re - (a == b ? 1.0 : 0.0)) > 1e-6 || std::fabs(im) > 1e-6) return false;
+    std::fill(gr, gr + d * d, 0.0);
+    std::fill(gi, gi + d * d, 0.0);
+    for (int r = 0; r < d; ++r) {
+      for (int c = 0; c < d; ++c) {
+        mr[c] = m[2 * (r * d + c)];
+        mi[c] = m[2 * (r * d + c) + 1];
       }
+      for (int a = 0; a < d; ++a) {  // (U^dagger U)[a][b] = sum_r conj(U[r][a]) U[r][b]
+        const double ar = mr[a], ai = mi[a];
+        double* __restrict__ xr = gr + a * d;
+        double* __restrict__ xi = gi + a * d;
+        for (int b = a; b < d; ++b) {
+          xr[b] += ar * mr[b] + ai * mi[b];
+          xi[b] += ar * mi[b] - ai * mr[b];
+        }
+      }
+    }
+    for (int a = 0; a < d; ++a)
+      for (int b = a; b < d; ++b)
+        if (std::fabs(gr[a * d + b] - (a == b ? 1.0 : 0.0)) > 1e-6 || std::fabs(gi[a * d + b]) > 1e-6) return false;
   }
   return true;
 }

@@ -20,6 +20,7 @@
 // blocks all of its qubits, controls included, for every other block.
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <condition_variable>
 #include <cstring>
 #include <exception>
@@ -119,8 +120,10 @@ void lower_controlled(const sv_gate* g, size_t n, int max_k, std::vector<sv_gate
 // imaginary parts held apart) and G acts on block-local bits pos[0..k-1]
 // (local bit j of G = block bit pos[j]).  The rows of M that differ only in
 // G's bits are combined whole, so the inner loop runs over contiguous columns.
+// `skip`: leave out products with zero entries (most of a diagonal or
+// permutation gate); only for blocks without infinities and NaNs.
 static void left_multiply(std::vector<double>& Mr, std::vector<double>& Mi, int K, const sv_gate& g,
-                          const int* pos) {
+                          const int* pos, bool skip) {
   const int d = 1 << K, k = g.k, dk = 1 << k;
   int sorted[SV_MAX_K];
   std::copy(pos, pos + k, sorted);
@@ -132,20 +135,22 @@ static void left_multiply(std::vector<double>& Mr, std::vector<double>& Mi, int 
       if ((l >> j) & 1) o |= 1 << pos[j];
     off[l] = o;
   }
-  std::vector<double> tr((size_t)dk * d), ti((size_t)dk * d);
+  constexpr int kMaxD = 1 << SV_MAX_K;
+  static thread_local double tr[kMaxD * kMaxD], ti[kMaxD * kMaxD];
   for (int grp = 0; grp < (d >> k); ++grp) {
     int base = grp;
     for (int j = 0; j < k; ++j) {
       const int lm = (1 << sorted[j]) - 1;
       base = ((base & ~lm) << 1) | (base & lm);
     }
-    std::fill(tr.begin(), tr.end(), 0.0);
-    std::fill(ti.begin(), ti.end(), 0.0);
     for (int r = 0; r < dk; ++r) {
-      double* __restrict__ orr = tr.data() + (size_t)r * d;
-      double* __restrict__ ori = ti.data() + (size_t)r * d;
+      double* __restrict__ orr = tr + (size_t)r * d;
+      double* __restrict__ ori = ti + (size_t)r * d;
+      std::fill(orr, orr + d, 0.0);
+      std::fill(ori, ori + d, 0.0);
       for (int c = 0; c < dk; ++c) {
         const double a = g.matrix[2 * (r * dk + c)], bb = g.matrix[2 * (r * dk + c) + 1];
+        if (skip && a == 0.0 && bb == 0.0) continue;
         const double* __restrict__ xr = Mr.data() + (size_t)(base + off[c]) * d;
         const double* __restrict__ xi = Mi.data() + (size_t)(base + off[c]) * d;
         for (int col = 0; col < d; ++col) {
@@ -155,10 +160,17 @@ static void left_multiply(std::vector<double>& Mr, std::vector<double>& Mi, int 
       }
     }
     for (int r = 0; r < dk; ++r) {
-      std::copy(tr.begin() + (size_t)r * d, tr.begin() + (size_t)(r + 1) * d, Mr.begin() + (size_t)(base + off[r]) * d);
-      std::copy(ti.begin() + (size_t)r * d, ti.begin() + (size_t)(r + 1) * d, Mi.begin() + (size_t)(base + off[r]) * d);
+      std::copy(tr + (size_t)r * d, tr + (size_t)(r + 1) * d, Mr.begin() + (size_t)(base + off[r]) * d);
+      std::copy(ti + (size_t)r * d, ti + (size_t)(r + 1) * d, Mi.begin() + (size_t)(base + off[r]) * d);
     }
   }
+}
+
+static bool all_finite(const sv_gate* g, const std::vector<int>& members) {
+  for (int i : members)
+    for (size_t e = 0; e < ((size_t)2 << (2 * g[i].k)); ++e)
+      if (!std::isfinite(g[i].matrix[e])) return false;
+  return true;
 }
 
 // Build the fused gate of an ordered member list.
@@ -184,10 +196,11 @@ static void build_block(const sv_gate* g, const std::vector<int>& members, Fused
   const int d = 1 << K;
   std::vector<double> Mr((size_t)d * d, 0.0), Mi((size_t)d * d, 0.0);
   for (int i = 0; i < d; ++i) Mr[(size_t)i * d + i] = 1.0;
+  const bool skip = all_finite(g, members);
   for (int i : members) {
     int pos[SV_MAX_K];
     for (int j = 0; j < g[i].k; ++j) pos[j] = bitpos[g[i].qubits[j]];
-    left_multiply(Mr, Mi, K, g[i], pos);
+    left_multiply(Mr, Mi, K, g[i], pos, skip);
   }
   out.mat.resize((size_t)2 * d * d);
   for (size_t i = 0; i < (size_t)d * d; ++i) {
@@ -248,6 +261,7 @@ static void build_block_mux(const sv_gate* g, const std::vector<int>& members, i
   }
   const int d = 1 << K;
   std::vector<double> Mr, Mi, dmat;
+  const bool skip = all_finite(g, members);
   for (int v = 0; v < (1 << nc); ++v) {
     uint64_t cval = 0;
     for (int t = 0; t < nc; ++t)
@@ -260,7 +274,7 @@ static void build_block_mux(const sv_gate* g, const std::vector<int>& members, i
       int pos[SV_MAX_K];
       if ((qmask(h) & Cm) == 0) {
         for (int j = 0; j < h.k; ++j) pos[j] = bitpos[h.qubits[j]];
-        left_multiply(Mr, Mi, K, h, pos);
+        left_multiply(Mr, Mi, K, h, pos, skip);
         continue;
       }
       // diagonal member reaching controls: its entries with the control bits fixed
@@ -297,7 +311,7 @@ static void build_block_mux(const sv_gate* g, const std::vector<int>& members, i
       rg.k = nt;
       for (int t = 0; t < nt; ++t) rg.qubits[t] = h.qubits[tj[t]];
       rg.matrix = dmat.data();
-      left_multiply(Mr, Mi, K, rg, pos);
+      left_multiply(Mr, Mi, K, rg, pos, skip);
     }
     FusedGate f;
     f.k = K;
@@ -769,7 +783,9 @@ void beam_partition(const sv_gate* g, size_t n, int max_k, int width, int topm,
   std::vector<BeamNode> beam(1);
   beam[0].live = proto.live;
   const unsigned hw = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
-  const unsigned nt = host_pool_worker() ? 1u : (unsigned)std::min<size_t>(hw, width);
+  // a round of a small circuit is shorter than waking a full pool for it
+  const size_t worth = std::max<size_t>(1, n * width / 1024);
+  const unsigned nt = host_pool_worker() ? 1u : (unsigned)std::min<size_t>(hw, std::min<size_t>(width, worth));
   std::vector<std::vector<BeamNode>> kids;
   std::atomic<size_t> next{0};
   std::vector<std::exception_ptr> errs(nt);

@@ -221,7 +221,7 @@ void encode_circuit(const CircPlan& c, unsigned char* dst) {
 template <class F>
 void for_circuits(size_t n_circ, F&& body) {
   const unsigned hw = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
-  const unsigned nt = (unsigned)std::min<size_t>(hw, std::max<size_t>(1, n_circ / 8));
+  const unsigned nt = (unsigned)std::min<size_t>(hw, std::max<size_t>(1, n_circ / 2));
   std::atomic<size_t> next{0};
   std::vector<std::exception_ptr> errs(nt);
   auto worker = [&](unsigned w) {
