@@ -170,7 +170,7 @@ static std::vector<unsigned char> graph_key(const std::vector<Launch>& launches,
   std::vector<int64_t> f;
   f.reserve(launches.size() * 22);
   for (const Launch& l : launches) {
-    f.insert(f.end(), {l.sweep.T, (int64_t)l.sweep.bits, (int64_t)l.sweep.mat_bytes, (int64_t)l.off, (int64_t)l.bytes});
+    f.insert(f.end(), {l.sweep.T, l.sweep.precision, (int64_t)l.sweep.bits, (int64_t)l.sweep.mat_bytes, (int64_t)l.off, (int64_t)l.bytes});
     if (l.sweep.T) continue;  // a sweep's passes are in its data
     const Pass& p = passes[l.sweep.members[0]];
     f.insert(f.end(), {p.k, p.variant, p.precision, p.tile_bits, p.reg_iters, p.mfma_cols, (int64_t)p.cmask,
@@ -310,7 +310,7 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
   std::vector<Launch> launches;
   {
     const bool sweeps = !timing && o.variant == SV_VARIANT_AUTO && s->n >= kSweepMinBits;
-    const int T = sweep_tile_bits(s->n);
+    const int T = sweep_tile_bits(s->n, o.precision);
     std::vector<SweepItem> items(passes.size());
     for (size_t i = 0; i < passes.size(); ++i) {
       const Pass& p = passes[i];
@@ -320,13 +320,13 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
       if (sweeps && p.variant != V_PHASE && !p.cmask) items[i].kind = sweep_kind(T, p.k, p.precision);
     }
     std::vector<Sweep> plan;
-    plan_sweeps(items, s->n, T, sweep_mat_room(T, T == s->n), plan);
+    plan_sweeps(items, s->n, T, sweep_mat_room(s->n, T, o.precision), o.precision, plan);
     launches.resize(plan.size());
     for (size_t i = 0; i < plan.size(); ++i) launches[i].sweep = std::move(plan[i]);
   }
   size_t total = 0;
   for (Launch& l : launches) {
-    if (l.sweep.T && (l.sweep.members.size() > 1 || passes[l.sweep.members[0]].k >= 5)) {
+    if (l.sweep.T && (l.sweep.members.size() > 1 || sweep_alone(s->n, passes[l.sweep.members[0]].k, o.precision))) {
       l.bytes = l.sweep.data_bytes;
     } else {
       l.sweep.T = 0;

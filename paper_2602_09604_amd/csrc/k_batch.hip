@@ -196,7 +196,7 @@ void plan_circuit(const sv_gate* g, size_t ng, int n, const sv_run_opts& o, Circ
     if (!items[i].kind) c.whole = true;
   }
   if (c.whole) return;
-  plan_sweeps(items, n, T, sweep_mat_room(T, false), c.sweeps);
+  plan_sweeps(items, n, T, sweep_mat_room(SV_MAX_QUBITS, T, SV_PREC_FP32_VALU), SV_PREC_FP32_VALU, c.sweeps);
   for (Sweep& s : c.sweeps) {
     c.off.push_back(c.bytes);
     c.bytes += (s.data_bytes + 255) / 256 * 256;

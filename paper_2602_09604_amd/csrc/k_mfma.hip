@@ -43,8 +43,8 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 constexpr int kLayoutPair = 0;  // bit 0 not a target: float4 = (group 2j, group 2j+1) at one amplitude
 constexpr int kLayoutQ0 = 1;    // bit 0 is target 0: float4 = amplitudes (2t, 2t+1) of one group
-constexpr float kF16Scale = 16384.f;       // 2^14
-constexpr float kF16LoScale = 2048.f;      // 2^11
+constexpr float kF16Scale = kSplitF16Scale;
+constexpr float kF16LoScale = kSplitF16LoScale;
 
 // ---- host-side conversions (round to nearest even) ------------------------
 uint16_t host_bf16(float f) {
@@ -698,6 +698,16 @@ bool mfma_supported(int k, int precision) {
 
 size_t mfma_data_bytes(const Pass& p) { return frag_bytes(p.k, p.precision) * (p.nmux > 1 ? p.nmux : 1); }
 
+void split_entry(int precision, double v, uint16_t& hi, uint16_t& lo) {
+  if (precision == SV_PREC_BF16X3) {
+    hi = host_bf16((float)v);
+    lo = host_bf16((float)(v - (double)host_bf16_to_f(hi)));
+  } else {
+    hi = host_f16((float)v);
+    lo = host_f16((float)((v - (double)host_f16_to_f(hi)) * (double)kF16LoScale));
+  }
+}
+
 // A' in fragment order.  FP32: [mt][s][lane] with lane (h, i) holding
 // A'[32 mt + i][2 s + h].  Split: [mt][s][part][lane][e] with lane (h, i)
 // holding A'[32 mt + i][16 s + 8 h + e]; part 0 = hi, part 1 = lo.
@@ -733,13 +743,7 @@ void mfma_encode(const Pass& p, const double* mat, unsigned char* dst) {
           const int h = lane >> 5, i = lane & 31;
           const double v = a4m(mat, dk, row_of(mt, i), split_col_of(s, h, e));
           uint16_t hi, lo;
-          if (p.precision == SV_PREC_BF16X3) {
-            hi = host_bf16((float)v);
-            lo = host_bf16((float)(v - (double)host_bf16_to_f(hi)));
-          } else {
-            hi = host_f16((float)v);
-            lo = host_f16((float)((v - (double)host_f16_to_f(hi)) * (double)kF16LoScale));
-          }
+          split_entry(p.precision, v, hi, lo);
           const size_t base = (((size_t)(mt * ks_n + s) * 2) * 64 + lane) * 8 + e;
           o[base] = hi;
           o[base + (size_t)64 * 8] = lo;

@@ -10,6 +10,8 @@
 // that a lane's inputs and its outputs are the same amplitudes, and a pass
 // reads and writes its tile in place with no exchange between lanes.  k = 1, 2
 // passes multiply on the vector ALUs, each lane on four amplitudes of its own.
+#include <type_traits>
+
 #include "k_common.h"
 #include "sweep.h"
 
@@ -19,6 +21,8 @@ namespace {
 using namespace kern;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((__vector_size__(8 * sizeof(short)))) short bf16x8;
+typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
 
 // Slots are float4 (two amplitudes); slot bits 0..3 are XORed with bits 4..7
 // and 8..11 so that strided accesses spread over the LDS banks.
@@ -119,6 +123,88 @@ __device__ __forceinline__ void op_mfma(unsigned char* tile, const SweepOp& op, 
   }
 }
 
+// The same pass with split operands (x = hi + lo, three products) on
+// v_mfma_f32_16x16x32: a k-step is four amplitudes of every lane.  The tile
+// holds FP32 amplitudes between passes, split as k_mfma.hip splits them.
+template <int T, int NW, int K, int PREC>
+__device__ __forceinline__ void op_split(unsigned char* tile, const SweepOp& op, const unsigned char* mats, int wave,
+                                         int lane) {
+  if constexpr (T >= K + 4) {
+    using frag = typename std::conditional<PREC == SV_PREC_BF16X3, bf16x8, f16x8>::type;
+    constexpr int IB = K - 2, N = 1 << IB, S = N / 4, RT = N / 2;
+    constexpr int UB = T - K - 4, UNITS = 1 << UB;
+    constexpr int UPW = UNITS >= NW ? UNITS / NW : 1;
+    constexpr int WPU = UNITS >= NW ? 1 : (NW / UNITS < RT ? NW / UNITS : RT);
+    constexpr int RTW = RT / WPU;
+    const bool on = wave < UNITS / UPW * WPU;
+    frag hi[UPW][S], lo[UPW][S];
+    uint32_t up[UPW];
+    if (on) {
+      const uint32_t lp = mix<6>(op, IB, ((lane & 15) << 2) | (lane >> 4));
+#pragma unroll
+      for (int u = 0; u < UPW; ++u) {
+        up[u] = lp ^ mix<UB>(op, IB + 6, wave / WPU * UPW + u);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          const float2 v = amp(tile, up[u] ^ mix<IB>(op, 0, i));
+#pragma unroll
+          for (int part = 0; part < 2; ++part) {
+            const float x = part ? v.y : v.x;
+            const int s = i / 4, e = 2 * (i % 4) + part;
+            if constexpr (PREC == SV_PREC_BF16X3) {
+              const short h = __builtin_bit_cast(short, (__bf16)x);
+              hi[u][s][e] = h;
+              lo[u][s][e] = __builtin_bit_cast(short, (__bf16)(x - __uint_as_float((uint32_t)(uint16_t)h << 16)));
+            } else {
+              const float xs = x * kSplitF16Scale;
+              const _Float16 h = (_Float16)xs;
+              hi[u][s][e] = h;
+              lo[u][s][e] = (_Float16)((xs - (float)h) * kSplitF16LoScale);
+            }
+          }
+        }
+      }
+    }
+    if constexpr (WPU > 1) tile_sync();
+    if (!on) return;
+    const frag* A = reinterpret_cast<const frag*>(mats + op.mat) + lane;  // [row tile][k-step][hi, lo][lane]
+    const int t0 = (wave % WPU) * RTW;
+#pragma unroll
+    for (int tt = 0; tt < RTW; ++tt) {
+      f32x4 acc[UPW], cor[UPW];
+#pragma unroll
+      for (int u = 0; u < UPW; ++u) acc[u] = cor[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const frag ah = A[(((t0 + tt) * S + s) * 2) * 64], al = A[(((t0 + tt) * S + s) * 2 + 1) * 64];
+#pragma unroll
+        for (int u = 0; u < UPW; ++u) {
+          if constexpr (PREC == SV_PREC_BF16X3) {
+            acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, hi[u][s], acc[u], 0, 0, 0);
+            acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, lo[u][s], acc[u], 0, 0, 0);
+            acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, hi[u][s], acc[u], 0, 0, 0);
+          } else {
+            acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, hi[u][s], acc[u], 0, 0, 0);
+            cor[u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, lo[u][s], cor[u], 0, 0, 0);
+            cor[u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, hi[u][s], cor[u], 0, 0, 0);
+          }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < UPW; ++u) {
+        float y[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          y[q] = PREC == SV_PREC_BF16X3 ? acc[u][q]
+                                        : (acc[u][q] + cor[u][q] * (1.f / kSplitF16LoScale)) * (1.f / kSplitF16Scale);
+#pragma unroll
+        for (int w = 0; w < 2; ++w)
+          amp(tile, up[u] ^ mix<IB>(op, 0, 2 * (t0 + tt) + w)) = make_float2(y[2 * w], y[2 * w + 1]);
+      }
+    }
+  }
+}
+
 // A one- or two-qubit pass on the vector ALUs: local bits are in-lane bits.
 template <int T, int NW, int K>
 __device__ __forceinline__ void op_valu(unsigned char* tile, const SweepOp& op, const unsigned char* __restrict__ data,
@@ -159,7 +245,8 @@ __device__ __forceinline__ void op_valu(unsigned char* tile, const SweepOp& op, 
 // and the matrix cores work at the same time (with one tile per workgroup the
 // workgroups of a launch stayed in step, all loading and then all
 // multiplying).  The matrices of the k >= 3 passes are copied to LDS once.
-template <int T, int NW, bool NT>
+// PREC: the split precision of the k >= 4 passes, or SV_PREC_FP32_MFMA.
+template <int T, int NW, bool NT, int PREC>
 __device__ __forceinline__ void sweep_tiles(float4* __restrict__ psi, const unsigned char* __restrict__ data,
                                             const SweepArgs& d, uint64_t t, uint64_t stride, unsigned char* smem) {
   unsigned char* tile = smem;
@@ -224,9 +311,15 @@ __device__ __forceinline__ void sweep_tiles(float4* __restrict__ psi, const unsi
         case 1: op_valu<T, NW, 1>(tile, op, data, wave, lane); break;
         case 2: op_valu<T, NW, 2>(tile, op, data, wave, lane); break;
         case 4: op_mfma<T, NW, 4>(tile, op, mats, wave, lane); break;
-        case 5: op_mfma<T, NW, 5>(tile, op, mats, wave, lane); break;
-        case 6: op_mfma<T, NW, 6>(tile, op, mats, wave, lane); break;
-        default: break;  // kinds are set on the host
+        default:  // kinds are set on the host
+          if constexpr (PREC == SV_PREC_FP32_MFMA) {
+            if (op.kind == 5) op_mfma<T, NW, 5>(tile, op, mats, wave, lane);
+            else op_mfma<T, NW, 6>(tile, op, mats, wave, lane);
+          } else {
+            if (op.kind == kSweepSplit + 4) op_split<T, NW, 4, PREC>(tile, op, mats, wave, lane);
+            else if (op.kind == kSweepSplit + 5) op_split<T, NW, 5, PREC>(tile, op, mats, wave, lane);
+            else op_split<T, NW, 6, PREC>(tile, op, mats, wave, lane);
+          }
       }
       tile_sync();
       op = ahead;
@@ -241,11 +334,11 @@ __device__ __forceinline__ void sweep_tiles(float4* __restrict__ psi, const unsi
   }
 }
 
-template <int T, int NW, bool NT>
+template <int T, int NW, bool NT, int PREC>
 __global__ __launch_bounds__(64 * NW) void k_sweep(float4* __restrict__ psi, const unsigned char* __restrict__ data,
                                                    const SweepArgs d) {
   extern __shared__ __align__(16) unsigned char smem[];
-  sweep_tiles<T, NW, NT>(psi, data, d, blockIdx.x, gridDim.x, smem);
+  sweep_tiles<T, NW, NT, PREC>(psi, data, d, blockIdx.x, gridDim.x, smem);
 }
 
 // The same sweeps of many states in one launch: entry e of the table owns
@@ -264,26 +357,36 @@ __global__ __launch_bounds__(512) void k_sweep_batch(const unsigned char* __rest
   const BatchSweep e = table[lo];
   const uint64_t t = b - e.first;
   switch (e.T) {
-    case 8: sweep_tiles<8, 8, NT>(e.psi, data + e.data, e.args, t, e.groups, smem); break;
-    case 9: sweep_tiles<9, 8, NT>(e.psi, data + e.data, e.args, t, e.groups, smem); break;
-    case 10: sweep_tiles<10, 8, NT>(e.psi, data + e.data, e.args, t, e.groups, smem); break;
-    case 11: sweep_tiles<11, 8, NT>(e.psi, data + e.data, e.args, t, e.groups, smem); break;
-    case 12: sweep_tiles<12, 8, NT>(e.psi, data + e.data, e.args, t, e.groups, smem); break;
+    case 8: sweep_tiles<8, 8, NT, SV_PREC_FP32_MFMA>(e.psi, data + e.data, e.args, t, e.groups, smem); break;
+    case 9: sweep_tiles<9, 8, NT, SV_PREC_FP32_MFMA>(e.psi, data + e.data, e.args, t, e.groups, smem); break;
+    case 10: sweep_tiles<10, 8, NT, SV_PREC_FP32_MFMA>(e.psi, data + e.data, e.args, t, e.groups, smem); break;
+    case 11: sweep_tiles<11, 8, NT, SV_PREC_FP32_MFMA>(e.psi, data + e.data, e.args, t, e.groups, smem); break;
+    case 12: sweep_tiles<12, 8, NT, SV_PREC_FP32_MFMA>(e.psi, data + e.data, e.args, t, e.groups, smem); break;
     default: break;  // tile sizes are set on the host
   }
 }
 
 constexpr uint64_t kSweepGroups = 512;  // workgroups of a launch: two per CU
 
-template <int T, int NW>
-void launch_t(const Sweep& sw, int n, void* psi, const unsigned char* data, hipStream_t st) {
+template <int T, int NW, int PREC>
+void launch_p(const Sweep& sw, int n, void* psi, const unsigned char* data, hipStream_t st) {
   const SweepArgs a = sweep_args(sw, n);
   const dim3 grid((unsigned)(a.tiles < kSweepGroups ? a.tiles : kSweepGroups));
   const size_t lds = ((size_t)8 << T) + sw.mat_bytes;
-  auto* kernel = n >= kNtMinQubits ? k_sweep<T, NW, true> : k_sweep<T, NW, false>;
+  auto* kernel = n >= kNtMinQubits ? k_sweep<T, NW, true, PREC> : k_sweep<T, NW, false, PREC>;
   if (lds > 65536)  // above the default limit of a workgroup's dynamic LDS
     SV_HIP(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), lds, st, (float4*)psi, data, a);
+}
+
+template <int T, int NW>
+void launch_t(const Sweep& sw, int n, void* psi, const unsigned char* data, hipStream_t st) {
+  if constexpr (T <= 12) {
+    if (sw.precision == SV_PREC_FP16X3) return launch_p<T, NW, SV_PREC_FP16X3>(sw, n, psi, data, st);
+    if (sw.precision == SV_PREC_BF16X3) return launch_p<T, NW, SV_PREC_BF16X3>(sw, n, psi, data, st);
+  }
+  if (sw.precision != SV_PREC_FP32_MFMA) throw DeviceError{hipErrorInvalidValue, "k_sweep: precision"};
+  launch_p<T, NW, SV_PREC_FP32_MFMA>(sw, n, psi, data, st);
 }
 
 }  // namespace

@@ -103,6 +103,11 @@ void launch_norm_noalloc(const void* psi, int n, double* out, hipStream_t st);
 size_t pass_data_bytes(const Pass& p);
 void encode_pass_data(const Pass& p, const double* mat, unsigned char* dst);
 bool mfma_supported(int k, int precision);
+// Split operands: hi and lo halves of a matrix entry, and the FP16 scales of
+// amplitudes and of the lo halves.
+constexpr float kSplitF16Scale = 16384.f;   // 2^14
+constexpr float kSplitF16LoScale = 2048.f;  // 2^11
+void split_entry(int precision, double v, uint16_t& hi, uint16_t& lo);
 int mfma_exchange_mask(int n, const Pass& p);
 // The register kernel streams a pass non-temporally with whole-line accesses:
 // no target on amplitude bits 1..3, or at most three element-space targets

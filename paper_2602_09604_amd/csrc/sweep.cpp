@@ -9,10 +9,17 @@
 namespace sv {
 
 namespace {
-// Device kind of a k-target pass: 1 and 2 on the vector ALUs, 4..6 on the
-// matrix cores (k = 3 padded with an identity bit).
-int op_kind(int k) { return k <= 2 ? k : std::max(k, 4); }
-size_t op_mat_bytes(int kind) { return (size_t)8 << (2 * kind); }  // complex64
+bool split_precision(int precision) { return precision == SV_PREC_BF16X3 || precision == SV_PREC_FP16X3; }
+// Device kind of a k-target pass: 1 and 2 on the vector ALUs, the others on
+// the matrix cores (k = 3 in FP32, padded with an identity bit).
+int op_kind(int k, int precision) {
+  if (k <= 2) return k;
+  return k == 3 ? 4 : split_precision(precision) ? kSweepSplit + k : k;
+}
+int kind_bits(int kind) { return kind > kSweepSplit ? kind - kSweepSplit : kind; }
+size_t op_mat_bytes(int kind) {  // complex64, or the real 2^(K+1) square matrix in two halves
+  return (size_t)(kind > kSweepSplit ? 16 : 8) << (2 * kind_bits(kind));
+}
 size_t lds_mat_bytes(int kind) { return kind > 2 ? op_mat_bytes(kind) : 0; }
 
 // byte-address mask of tile bit b (the swizzle of k_sweep.hip on one bit)
@@ -24,7 +31,8 @@ uint32_t bit_mask(int b) {
 }  // namespace
 
 // Tile size of an n-qubit state.
-int sweep_tile_bits(int n) {
+int sweep_tile_bits(int n, int precision) {
+  if (split_precision(precision)) return std::min(n, 12);  // room for two 64 KiB matrices
   return n <= 20 ? std::min(n, 12) : 13;
 }
 
@@ -32,16 +40,25 @@ int sweep_tile_bits(int n) {
 // for k >= 4), as long as the tile holds one unit of 16 groups.
 int sweep_kind(int T, int k, int precision) {
   if (std::max(k, 4) + 4 > T) return 0;
-  if (k >= 4 && precision != SV_PREC_FP32_VALU && precision != SV_PREC_FP32_MFMA) return 0;
-  return op_kind(k);
+  return op_kind(k, precision);
 }
+
+// FP32: from k = 5, where the register kernel is bound by its ALUs (one
+// 5-qubit gate at 28 qubits 1060-1612 us there, 774-820 us here; 12 to 20
+// qubits 70-80 us there, 24 here) and the FP32 pass of k_mfma.hip by its
+// larger instructions (793-892 us; 6 qubits 1440-1556 against 1502); at k = 4
+// the pass kernels are as fast. Split precisions: up to 20 qubits (5 qubits 36
+// -> 30 us in FP16X3); above, k_mfma.hip's passes stream better (28 qubits 711
+// against 892 us).
+bool sweep_alone(int n, int k, int precision) { return k >= 5 && (!split_precision(precision) || n <= 20); }
 
 // Greedy in passes: a sweep is seeded with the first pass left and takes
 // every later eligible pass whose targets still fit in the tile and which
 // shares no qubit with a pass skipped before it (so it commutes with all of
 // those).  A pass that is not eligible is a sweep of its own (T = 0) and keeps
 // its place in the order.
-void plan_sweeps(const std::vector<SweepItem>& items, int n, int T, size_t mat_room, std::vector<Sweep>& out) {
+void plan_sweeps(const std::vector<SweepItem>& items, int n, int T, size_t mat_room, int precision,
+                 std::vector<Sweep>& out) {
   out.clear();
   const int low = T == n ? T : kSweepLow;
   const uint64_t low_mask = ((uint64_t)1 << low) - 1;
@@ -53,6 +70,7 @@ void plan_sweeps(const std::vector<SweepItem>& items, int n, int T, size_t mat_r
     used[s] = 1;
     if (items[s].kind) {
       sw.T = T;
+      if (split_precision(precision)) sw.precision = precision;
       sw.low = low;
       sw.bits = low_mask | items[s].mask;
       size_t mat = lds_mat_bytes(items[s].kind);
@@ -103,9 +121,9 @@ void encode_sweep(const Sweep& sw, const std::vector<const Pass*>& passes, const
   const size_t big_off = sw.data_bytes - sw.mat_bytes;
   for (size_t p = 0; p < passes.size(); ++p) {
     const Pass& ps = *passes[p];
-    const int k = ps.k, K = op_kind(k);
+    const int k = ps.k, kind = op_kind(k, ps.precision), K = kind_bits(kind);
     SweepOp op{};
-    op.kind = (uint32_t)K;
+    op.kind = (uint32_t)kind;
     op.mat = (uint32_t)(K <= 2 ? at : big);
     // roles of the tile bits: the local bits (targets, then identity bits),
     // lane bits, unit bits.  The lane bits j, and with them h, should fall on
@@ -138,9 +156,28 @@ void encode_sweep(const Sweep& sw, const std::vector<const Pass*>& passes, const
     std::memcpy(dst + p * sizeof(SweepOp), &op, sizeof(op));
     const double* m = mats[p];
     float* f = reinterpret_cast<float*>(dst + (K <= 2 ? at : big_off + big));
-    (K <= 2 ? at : big) += op_mat_bytes(K);
+    (K <= 2 ? at : big) += op_mat_bytes(kind);
     if (K <= 2) {
       for (size_t e = 0; e < (size_t)2 << (2 * K); ++e) f[e] = (float)m[e];
+      continue;
+    }
+    if (kind > kSweepSplit) {
+      // [row tile t][k-step s][hi, lo][lane][e]: entry e of lane (h, j) is row
+      // (amplitude (j / 4) N + 2 t + (j / 2) % 2, part j % 2), column
+      // (amplitude h N + 4 s + e / 2, part e % 2)
+      const int N = 1 << (K - 2), D = 1 << K;
+      uint16_t* o = reinterpret_cast<uint16_t*>(f);
+      for (int t = 0; t < N / 2; ++t)
+        for (int s = 0; s < N / 4; ++s, o += 2 * 64 * 8)
+          for (int lane = 0; lane < 64; ++lane) {
+            const int h = lane >> 4, j = lane & 15;
+            const int row = (j >> 2) * N + 2 * t + ((j >> 1) & 1), rp = j & 1;
+            for (int e = 0; e < 8; ++e) {
+              const int col = h * N + 4 * s + (e >> 1), cp = e & 1;
+              const double ur = m[2 * ((size_t)row * D + col)], ui = m[2 * ((size_t)row * D + col) + 1];
+              split_entry(ps.precision, rp == cp ? ur : rp == 0 ? -ui : ui, o[lane * 8 + e], o[64 * 8 + lane * 8 + e]);
+            }
+          }
       continue;
     }
     // [row tile t][column pair i2][h][row r of 8]: lane h holds the

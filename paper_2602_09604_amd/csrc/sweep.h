@@ -10,12 +10,23 @@ namespace sv {
 
 constexpr int kSweepMaxBits = 13;  // largest tile: 2^13 amplitudes, 64 KiB of LDS
 constexpr int kSweepMinBits = 8;   // one matrix-core unit of a k = 4 pass
-// LDS for the matrices of a sweep: so that two workgroups share a CU's 160 KiB
-// (a sweep of one larger matrix takes more and runs alone), or, where the
-// state is a single tile, all of it.
-constexpr size_t sweep_mat_room(int T, bool one_tile) { return (one_tile ? 163840 : 81920) - ((size_t)8 << T); }
+// LDS for the matrices of a sweep of an n-qubit state: so that two workgroups
+// share a CU's 160 KiB (a sweep of one larger matrix takes more and runs
+// alone), or all of it where the state is a single tile and, for split
+// matrices (64 KiB at k = 6), up to 20 qubits, where a CU has one tile anyway,
+// and from 25, where the sweep saved is worth more than the second workgroup
+// (two k = 6 passes in a sweep: 26 qubits 4305 -> 4165 us for 20 passes, 22
+// qubits 291 -> 306 us for 15).
+inline size_t sweep_mat_room(int n, int T, int precision) {
+  const bool split = precision == SV_PREC_BF16X3 || precision == SV_PREC_FP16X3;
+  const bool all = T == n || (split && (n <= 20 || n >= 25));
+  return (all ? 163840 : 81920) - ((size_t)8 << T);
+}
 constexpr int kSweepLow = 4;       // low state bits in every tile: whole 128-byte lines
 constexpr int kSweepMaxK = 6;
+
+// Kind of a K-qubit pass in the sweep's split precision.
+constexpr int kSweepSplit = 8;
 
 // One pass of a sweep on the device.  Tile bits are numbered in the order
 // in-lane bits (K - 2 of them; for K = 2 both local bits), two lane bits h,
@@ -24,7 +35,7 @@ constexpr int kSweepMaxK = 6;
 // the bits, so any assignment of state bits to these roles is one table.
 struct alignas(64) SweepOp {
   uint32_t mask[kSweepMaxBits];
-  uint32_t kind;   // 1, 2: vector ALUs; 4..6: FP32 matrix cores
+  uint32_t kind;   // 1, 2: vector ALUs; 4..6: FP32 matrix cores; kSweepSplit + 4..6: split operands
   uint32_t mat;    // byte offset of the matrix: kinds 1, 2 from the sweep's data, the others in the LDS copy
 };
 
@@ -48,6 +59,7 @@ struct Sweep {
   int low = 0;
   uint64_t bits = 0;            // state bits in the tile
   std::vector<int> members;
+  int precision = SV_PREC_FP32_MFMA;  // of the k >= 4 passes
   size_t mat_bytes = 0;         // LDS bytes of the matrices
   size_t data_bytes = 0;        // device data: the passes and every matrix
 };
@@ -69,11 +81,14 @@ struct SweepItem {
   int kind = 0;
 };
 
-int sweep_tile_bits(int n);
+int sweep_tile_bits(int n, int precision);
 // Device kind of a k-target pass in a sweep with tiles of T bits; 0: it does not run in one.
 int sweep_kind(int T, int k, int precision);
+// Whether a pass that shares its sweep with no other still runs as one.
+bool sweep_alone(int n, int k, int precision);
 // T: tile size, at most n; mat_room: LDS bytes for the matrices of a sweep.
-void plan_sweeps(const std::vector<SweepItem>& items, int n, int T, size_t mat_room, std::vector<Sweep>& out);
+void plan_sweeps(const std::vector<SweepItem>& items, int n, int T, size_t mat_room, int precision,
+                 std::vector<Sweep>& out);
 SweepArgs sweep_args(const Sweep& sw, int n);
 // Encode one sweep: targets (sorted) and matrix of every pass, in order.
 void encode_sweep(const Sweep& sw, const std::vector<const Pass*>& passes, const std::vector<const double*>& mats,

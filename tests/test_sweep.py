@@ -4,7 +4,9 @@ of a k = 4 pass), a whole state in one tile, the first states of several
 tiles, and a streamed state.
 
 Bar: max |delta amplitude| <= 1e-5 and infidelity <= 1e-6 (complex64 state,
-FP32 arithmetic, a few hundred passes), as for the single passes."""
+FP32 arithmetic, a few hundred passes), as for the single passes; BF16 splits
+carry 16 bits, so on the smallest states, whose amplitudes are large, their
+amplitudes are held to 2^-16 times the root of the pass count."""
 import numpy as np
 import pytest
 
@@ -36,7 +38,8 @@ def mixed_circuit(n, gates, max_k, seed):
 
 @pytest.mark.parametrize("n", [7, 8, 9, 10, 11, 12, 13, 14, 17, 20, 21, 22, 26])
 @pytest.mark.parametrize("fusion,max_k,precision", [("none", 1, "fp32_valu"), ("greedy", 4, "fp32_valu"),
-                                                    ("greedy", 5, "fp32_mfma"), ("phase", 3, "fp16x3")])
+                                                    ("greedy", 5, "fp32_mfma"), ("phase", 3, "fp16x3"),
+                                                    ("greedy", 4, "bf16x3"), ("greedy", 6, "fp16x3")])
 def test_sweeps_against_oracle(n, fusion, max_k, precision):
     from paper_2602_09604_amd import sv
     gates = mixed_circuit(n, 24 if n == 26 else 90, 6 if fusion == "none" else 3, 100 + n)
@@ -52,8 +55,9 @@ def test_sweeps_against_oracle(n, fusion, max_k, precision):
     assert s["launches"] <= s["passes"]
     if n >= 8 and fusion == "none":
         assert s["launches"] < s["passes"]
-    assert r["max_abs"] <= MAX_ABS and r["infidelity"] <= INFID, r
-    assert abs(norm - 1.0) <= 1e-5
+    bar = max(MAX_ABS, 2.0 ** -16 * s["passes"] ** 0.5) if precision == "bf16x3" else MAX_ABS
+    assert r["max_abs"] <= bar and r["infidelity"] <= INFID, r
+    assert abs(norm - 1.0) <= (1e-4 if precision == "bf16x3" else 1e-5)
 
 
 @pytest.mark.parametrize("n", [12, 22])
