@@ -285,6 +285,9 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
       continue;
     }
     p.variant = choose_variant(s->n, p.k, p.s, o.precision, o.variant == SV_VARIANT_SHFL ? V_SHFL : o.variant);
+    // passes the split matrix cores do not take (k = 5, 6 on states below k + 6
+    // qubits, or by the tuned table) run in FP32, in a sweep too
+    if (p.k >= 4 && p.variant != V_MFMA) p.precision = SV_PREC_FP32_VALU;
     const Shape sh = tuned_shape(p.variant, s->n, p.k, p.s, o.precision);
     p.tile_bits = sh.tile_bits;
     p.reg_iters = sh.reg_iters;
@@ -326,7 +329,7 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
   }
   size_t total = 0;
   for (Launch& l : launches) {
-    if (l.sweep.T && (l.sweep.members.size() > 1 || sweep_alone(s->n, passes[l.sweep.members[0]].k, o.precision))) {
+    if (l.sweep.T && (l.sweep.members.size() > 1 || sweep_alone(s->n, passes[l.sweep.members[0]].k, passes[l.sweep.members[0]].precision))) {
       l.bytes = l.sweep.data_bytes;
     } else {
       l.sweep.T = 0;

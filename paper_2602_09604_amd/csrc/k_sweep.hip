@@ -312,14 +312,13 @@ __device__ __forceinline__ void sweep_tiles(float4* __restrict__ psi, const unsi
         case 2: op_valu<T, NW, 2>(tile, op, data, wave, lane); break;
         case 4: op_mfma<T, NW, 4>(tile, op, mats, wave, lane); break;
         default:  // kinds are set on the host
-          if constexpr (PREC == SV_PREC_FP32_MFMA) {
-            if (op.kind == 5) op_mfma<T, NW, 5>(tile, op, mats, wave, lane);
-            else op_mfma<T, NW, 6>(tile, op, mats, wave, lane);
-          } else {
+          if constexpr (PREC != SV_PREC_FP32_MFMA) {
             if (op.kind == kSweepSplit + 4) op_split<T, NW, 4, PREC>(tile, op, mats, wave, lane);
             else if (op.kind == kSweepSplit + 5) op_split<T, NW, 5, PREC>(tile, op, mats, wave, lane);
-            else op_split<T, NW, 6, PREC>(tile, op, mats, wave, lane);
+            else if (op.kind == kSweepSplit + 6) op_split<T, NW, 6, PREC>(tile, op, mats, wave, lane);
           }
+          if (op.kind == 5) op_mfma<T, NW, 5>(tile, op, mats, wave, lane);
+          else if (op.kind == 6) op_mfma<T, NW, 6>(tile, op, mats, wave, lane);
       }
       tile_sync();
       op = ahead;
