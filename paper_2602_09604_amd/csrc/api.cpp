@@ -379,6 +379,9 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
     if (timing) SV_HIP(hipEventRecord(s->pass_events[2 * i + 1], s->stream));
   };
   if (graph) {
+    // the key compares every byte, also those between the launches' data,
+    // where the ring may hold an earlier call's
+    std::memset(s->arena_host + base, 0, total);
     for (size_t i = 0; i < launches.size(); ++i) encode(i);
     // The graph reads its pass data from its own buffer, so ring uploads of
     // later calls never disturb it; relaunch when nothing it encodes changed.

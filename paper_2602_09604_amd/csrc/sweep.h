@@ -33,10 +33,11 @@ constexpr int kSweepSplit = 8;
 // four lane bits j, then unit bits; mask[b] is what bit b adds (by XOR) to a
 // byte address in the tile: the swizzle of the tile's slots is linear over
 // the bits, so any assignment of state bits to these roles is one table.
-struct alignas(64) SweepOp {
+struct alignas(64) SweepOp {  // 64 bytes, no padding: graph keys compare the data
   uint32_t mask[kSweepMaxBits];
   uint32_t kind;   // 1, 2: vector ALUs; 4..6: FP32 matrix cores; kSweepSplit + 4..6: split operands
   uint32_t mat;    // byte offset of the matrix: kinds 1, 2 from the sweep's data, the others in the LDS copy
+  uint32_t unused;
 };
 
 // Launch arguments of a sweep.  hi packs the state bits of the tile above its
