@@ -8,8 +8,10 @@
 // of a unit (16 groups of 2^K amplitudes) holds the amplitudes h 2^(K-2) + i of
 // group j: the rows and columns of the real matrix are ordered on the host so
 // that a lane's inputs and its outputs are the same amplitudes, and a pass
-// reads and writes its tile in place with no exchange between lanes.  k = 1, 2
-// passes multiply on the vector ALUs, each lane on four amplitudes of its own.
+// reads and writes its tile in place with no exchange between lanes.  No pass
+// is padded to a larger one: products with the zeros of a padding would carry an
+// infinite or NaN amplitude out of its group.  k = 1, 2 passes multiply on the
+// vector ALUs, each lane on four amplitudes of its own.
 #include <type_traits>
 
 #include "k_common.h"
@@ -314,6 +316,7 @@ __device__ __forceinline__ void sweep_tiles(float4* __restrict__ psi, const unsi
       switch (op.kind) {
         case 1: op_valu<T, NW, 1>(tile, op, data, wave, lane); break;
         case 2: op_valu<T, NW, 2>(tile, op, data, wave, lane); break;
+        case 3: op_mfma<T, NW, 3>(tile, op, mats, wave, lane); break;
         case 4: op_mfma<T, NW, 4>(tile, op, mats, wave, lane); break;
         default:  // kinds are set on the host
           if constexpr (PREC != SV_PREC_FP32_MFMA) {

@@ -11,11 +11,8 @@ namespace sv {
 namespace {
 bool split_precision(int precision) { return precision == SV_PREC_BF16X3 || precision == SV_PREC_FP16X3; }
 // Device kind of a k-target pass: 1 and 2 on the vector ALUs, the others on
-// the matrix cores (k = 3 in FP32, padded with an identity bit).
-int op_kind(int k, int precision) {
-  if (k <= 2) return k;
-  return k == 3 ? 4 : split_precision(precision) ? kSweepSplit + k : k;
-}
+// the matrix cores (k = 3 always in FP32).
+int op_kind(int k, int precision) { return k >= 4 && split_precision(precision) ? kSweepSplit + k : k; }
 int kind_bits(int kind) { return kind > kSweepSplit ? kind - kSweepSplit : kind; }
 size_t op_mat_bytes(int kind) {  // complex64, or the real 2^(K+1) square matrix in two halves
   return (size_t)(kind > kSweepSplit ? 16 : 8) << (2 * kind_bits(kind));
@@ -121,26 +118,26 @@ void encode_sweep(const Sweep& sw, const std::vector<const Pass*>& passes, const
   const size_t big_off = sw.data_bytes - sw.mat_bytes;
   for (size_t p = 0; p < passes.size(); ++p) {
     const Pass& ps = *passes[p];
-    const int k = ps.k, kind = op_kind(k, ps.precision), K = kind_bits(kind);
+    const int K = ps.k, kind = op_kind(K, ps.precision);
     SweepOp op{};
     op.kind = (uint32_t)kind;
     op.mat = (uint32_t)(K <= 2 ? at : big);
-    // roles of the tile bits: the local bits (targets, then identity bits),
-    // lane bits, unit bits.  The lane bits j, and with them h, should fall on
+    // roles of the tile bits: the local bits (targets; for K = 1 one more in-lane
+    // bit), lane bits, unit bits.  The lane bits j, and with them h, should fall on
     // different banks: bit 0 and tile bits b with different (b - 1) % 4.
-    const int nl = std::max(K, 2);  // in-lane and h bits for K >= 4; the two in-lane bits for K <= 2
+    const int nl = std::max(K, 2);  // in-lane and h bits for K >= 3; the two in-lane bits for K <= 2
     bool taken[kSweepMaxBits] = {};
     int role[kSweepMaxBits], nr = 0;
-    for (int j = 0; j < k; ++j) {
+    for (int j = 0; j < K; ++j) {
       role[nr++] = tile_bit[ps.s[j]];
       taken[role[nr - 1]] = true;
     }
     auto cls = [](int b) { return b == 0 ? 4 : (b - 1) & 3; };
-    for (int b = sw.T - 1; b >= 0 && nr < nl; --b)  // identity bits from the top
+    for (int b = sw.T - 1; b >= 0 && nr < nl; --b)  // the in-lane bit left at K = 1, from the top
       if (!taken[b]) taken[role[nr++] = b] = true;
     bool cls_used[5] = {};
     const int lanes = K <= 2 ? 6 : 4;
-    if (K >= 4) cls_used[cls(role[K - 2])] = true;  // h bit 0
+    if (K >= 3) cls_used[cls(role[K - 2])] = true;  // h bit 0
     int got = 0;
     for (int pass = 0; pass < 2 && got < lanes; ++pass)  // distinct classes first, then any
       for (int b = 0; b < sw.T && got < lanes; ++b) {
@@ -182,16 +179,14 @@ void encode_sweep(const Sweep& sw, const std::vector<const Pass*>& passes, const
     }
     // [row tile t][column pair i2][h][row r of 8]: lane h holds the
     // amplitudes h N + i; row r of tile t is amplitude (r / 2) N + 2 t + r % 2
-    const int N = 1 << (K - 2), dk = 1 << k;
+    const int N = 1 << (K - 2), D = 1 << K;
     for (int t = 0; t < N / 2; ++t)
       for (int i2 = 0; i2 < N / 2; ++i2)
         for (int h = 0; h < 4; ++h)
           for (int r = 0; r < 8; ++r)
             for (int w = 0; w < 2; ++w, f += 2) {
               const int row = (r >> 1) * N + 2 * t + (r & 1), col = h * N + 2 * i2 + w;
-              f[0] = f[1] = 0.f;
-              if ((row >> k) != (col >> k)) continue;  // identity on the padding bits
-              const size_t e = (size_t)2 * ((row & (dk - 1)) * dk + (col & (dk - 1)));
+              const size_t e = (size_t)2 * (row * D + col);
               f[0] = (float)m[e];
               f[1] = (float)m[e + 1];
             }

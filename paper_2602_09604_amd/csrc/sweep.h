@@ -35,7 +35,7 @@ constexpr int kSweepSplit = 8;
 // the bits, so any assignment of state bits to these roles is one table.
 struct alignas(64) SweepOp {  // 64 bytes, no padding: graph keys compare the data
   uint32_t mask[kSweepMaxBits];
-  uint32_t kind;   // 1, 2: vector ALUs; 4..6: FP32 matrix cores; kSweepSplit + 4..6: split operands
+  uint32_t kind;   // 1, 2: vector ALUs; 3..6: FP32 matrix cores; kSweepSplit + 4..6: split operands
   uint32_t mat;    // byte offset of the matrix: kinds 1, 2 from the sweep's data, the others in the LDS copy
   uint32_t unused;
 };
@@ -49,7 +49,7 @@ struct SweepArgs {
   int32_t low = 0;      // L
   int32_t nh = 0;       // T - L
   int32_t nops = 0;
-  int32_t mat16 = 0;    // LDS copy of the matrices of kinds 4..6, in 16-byte units
+  int32_t mat16 = 0;    // LDS copy of the matrices of kinds 3 and up, in 16-byte units
   uint32_t mat_off = 0; // where they start in the data (the passes come first)
 };
 
