@@ -100,6 +100,7 @@ __global__ __launch_bounds__(256) void k_phase(float4* __restrict__ psi, const u
     }
   }
 
+  static_assert(kPhaseCoefBytes % alignof(double4) == 0, "the table follows the coefficients");
   const double4* tab = reinterpret_cast<const double4*>(data + kPhaseCoefBytes);
   const uint64_t span = (uint64_t)1 << (a.lb - 1);  // elements per sweep of the grid
   const uint64_t sweeps = (uint64_t)1 << a.nh;

@@ -209,7 +209,8 @@ struct PhasePoly {
 constexpr int kPhaseMaxQ = SV_MAX_QUBITS;
 constexpr int kPhaseLowBits = 28;
 constexpr int kPhaseMaxHigh = kPhaseMaxQ - kPhaseLowBits;
-constexpr size_t kPhaseCoefBytes = ((1 + kPhaseMaxQ + (size_t)kPhaseMaxQ * kPhaseMaxQ) * sizeof(double) + 15) / 16 * 16;
+// the table that follows is read as double4, 32-byte aligned
+constexpr size_t kPhaseCoefBytes = ((1 + kPhaseMaxQ + (size_t)kPhaseMaxQ * kPhaseMaxQ) * sizeof(double) + 31) / 32 * 32;
 constexpr int kPhaseMinLowBits = 20;
 inline int phase_low_bits(int n) {
   if (n <= kPhaseMinLowBits) return n;
