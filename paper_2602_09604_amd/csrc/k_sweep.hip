@@ -372,6 +372,15 @@ __global__ __launch_bounds__(512) void k_sweep_batch(const unsigned char* __rest
   }
 }
 
+// Lets a kernel take the most dynamic LDS any sweep asks for.  The limit belongs
+// to the kernel, not to a launch: threads launch sweeps of different sizes at
+// the same time, so every one of them sets the same value.
+void allow_lds(const void* kernel, size_t lds) {
+  if (lds > kSweepLds) throw DeviceError{hipErrorInvalidValue, "k_sweep: LDS of a workgroup"};
+  if (lds > 65536)  // above the default limit
+    SV_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSweepLds));
+}
+
 constexpr uint64_t kSweepGroups = 512;  // workgroups of a launch: two per CU
 
 template <int T, int NW, int PREC>
@@ -380,8 +389,7 @@ void launch_p(const Sweep& sw, int n, void* psi, const unsigned char* data, hipS
   const dim3 grid((unsigned)(a.tiles < kSweepGroups ? a.tiles : kSweepGroups));
   const size_t lds = ((size_t)8 << T) + sw.mat_bytes;
   auto* kernel = n >= kNtMinQubits ? k_sweep<T, NW, true, PREC> : k_sweep<T, NW, false, PREC>;
-  if (lds > 65536)  // above the default limit of a workgroup's dynamic LDS
-    SV_HIP(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  allow_lds((const void*)kernel, lds);
   hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), lds, st, (float4*)psi, data, a);
 }
 
@@ -414,8 +422,7 @@ void launch_sweep(const Sweep& sw, int n, void* psi, const unsigned char* data, 
 void launch_sweep_batch(const BatchSweep* table, int count, unsigned groups, size_t lds, bool nt,
                         const unsigned char* data, hipStream_t st) {
   auto* kernel = nt ? k_sweep_batch<true> : k_sweep_batch<false>;
-  if (lds > 65536)
-    SV_HIP(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  allow_lds((const void*)kernel, lds);
   hipLaunchKernelGGL(kernel, dim3(groups), dim3(512), lds, st, data, table, count);
   SV_HIP(hipGetLastError());
 }

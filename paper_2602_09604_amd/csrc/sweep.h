@@ -10,6 +10,7 @@ namespace sv {
 
 constexpr int kSweepMaxBits = 13;  // largest tile: 2^13 amplitudes, 64 KiB of LDS
 constexpr int kSweepMinBits = 8;   // one matrix-core unit of a k = 4 pass
+constexpr size_t kSweepLds = 163840;  // what a workgroup may take: a CU's 160 KiB
 // LDS for the matrices of a sweep of an n-qubit state: so that two workgroups
 // share a CU's 160 KiB (a sweep of one larger matrix takes more and runs
 // alone), or all of it where the state is a single tile and, for split
@@ -20,7 +21,7 @@ constexpr int kSweepMinBits = 8;   // one matrix-core unit of a k = 4 pass
 inline size_t sweep_mat_room(int n, int T, int precision) {
   const bool split = precision == SV_PREC_BF16X3 || precision == SV_PREC_FP16X3;
   const bool all = T == n || (split && (n <= 20 || n >= 25));
-  return (all ? 163840 : 81920) - ((size_t)8 << T);
+  return (all ? kSweepLds : kSweepLds / 2) - ((size_t)8 << T);
 }
 constexpr int kSweepLow = 4;       // low state bits in every tile: whole 128-byte lines
 constexpr int kSweepMaxK = 6;
