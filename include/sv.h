@@ -283,8 +283,10 @@ int sv_norm_noalloc(const void* dev_state, int n_qubits, size_t buf_bytes, void*
  * string with X on the qubits of xmask[t] only, Z on zmask[t] only and Y on
  * both; out[t] = <psi|P_t|psi> (real: P_t is Hermitian), not divided by
  * <psi|psi>.  Products are formed in FP32 from the complex64 amplitudes and
- * accumulated in FP64.  Terms that share an X/Y part share one sweep of the
- * state (up to 8 terms per sweep).  Synchronises the handle's stream.
+ * accumulated in FP64 in an order that depends on n and the term alone, so a
+ * term's value does not depend on the others of the call.  Terms that share an
+ * X/Y part share one sweep of the state (up to 8 terms per sweep).  Device
+ * scratch up to 8 MiB stays with the handle.  Synchronises the handle's stream.
  * SV_EINVAL: a mask reaches past n, n_terms > 0 with NULL arrays. */
 int sv_expect_pauli(sv_state* s, size_t n_terms, const uint64_t* xmask, const uint64_t* zmask, double* out);
 

@@ -950,38 +950,34 @@ int sv_expect_pauli(sv_state* s, size_t n_terms, const uint64_t* xmask, const ui
     }
   }
   // the sums land in pinned host memory, written by the kernel itself
-  const size_t per_call = std::min(sweep_f.size(), kPauliSweepsMax);
-  meas_reserve(s, pauli_scratch_bytes(s->n, per_call), sizeof(double) * 8 * per_call);
+  meas_reserve(s, pauli_scratch_bytes(s->n, sweep_f.size()), sizeof(double) * 8 * sweep_f.size());
   const double* h = reinterpret_cast<const double*>(s->meas_host);
-  std::vector<PauliSweep> sweeps;
+  std::vector<PauliSweep> sweeps(sweep_f.size());
   std::vector<int> order;
-  for (size_t w0 = 0; w0 < sweep_f.size(); w0 += per_call) {
-    sweeps.assign(std::min(per_call, sweep_f.size() - w0), PauliSweep{});
-    for (size_t w = 0; w < sweeps.size(); ++w) {
-      sweeps[w].f = sweep_f[w0 + w];
-      sweeps[w].terms = (int)sweep_terms[w0 + w].size();
-      for (int j = 0; j < sweeps[w].terms; ++j) sweeps[w].z[j] = zmask[sweep_terms[w0 + w][j]];
-    }
-    launch_pauli(s->psi, s->n, sweeps, order, reinterpret_cast<double*>(s->meas_dev),
-                 reinterpret_cast<double*>(s->meas_host), s->stream);
-    SV_HIP(hipStreamSynchronize(s->stream));
-    for (size_t i = 0; i < order.size(); ++i) {
-      const uint64_t f = sweeps[order[i]].f;
-      const std::vector<size_t>& terms = sweep_terms[w0 + order[i]];
-      for (size_t j = 0; j < terms.size(); ++j) {
-        const uint64_t z = zmask[terms[j]];
-        // sum_i (-1)^{|(i^f) & z|} conj(c_i) c_{i^f}: a pair's two terms add
-        // up to 2 Re w for an even |f & z| and -2i Im w for an odd one
-        const double v = f ? 2.0 * h[8 * i + j] : h[8 * i + j];
-        const bool odd = __builtin_popcountll(f & z) & 1;
-        const double re = odd ? 0.0 : v, im = odd ? -v : 0.0;
-        // P = i^ny X^f Z^z with ny = |f & z| (the Y letters): Re(i^ny (re + i im))
-        switch (__builtin_popcountll(f & z) & 3) {
-          case 0: out[terms[j]] = re; break;
-          case 1: out[terms[j]] = -im; break;
-          case 2: out[terms[j]] = -re; break;
-          default: out[terms[j]] = im; break;
-        }
+  for (size_t w = 0; w < sweeps.size(); ++w) {
+    sweeps[w].f = sweep_f[w];
+    sweeps[w].terms = (int)sweep_terms[w].size();
+    for (int j = 0; j < sweeps[w].terms; ++j) sweeps[w].z[j] = zmask[sweep_terms[w][j]];
+  }
+  launch_pauli(s->psi, s->n, sweeps, order, reinterpret_cast<double*>(s->meas_dev),
+               reinterpret_cast<double*>(s->meas_host), s->stream);
+  SV_HIP(hipStreamSynchronize(s->stream));
+  for (size_t i = 0; i < order.size(); ++i) {
+    const uint64_t f = sweeps[order[i]].f;
+    const std::vector<size_t>& terms = sweep_terms[order[i]];
+    for (size_t j = 0; j < terms.size(); ++j) {
+      const uint64_t z = zmask[terms[j]];
+      // sum_i (-1)^{|(i^f) & z|} conj(c_i) c_{i^f}: a pair's two terms add
+      // up to 2 Re w for an even |f & z| and -2i Im w for an odd one
+      const double v = f ? 2.0 * h[8 * i + j] : h[8 * i + j];
+      const bool odd = __builtin_popcountll(f & z) & 1;
+      const double re = odd ? 0.0 : v, im = odd ? -v : 0.0;
+      // P = i^ny X^f Z^z with ny = |f & z| (the Y letters): Re(i^ny (re + i im))
+      switch (__builtin_popcountll(f & z) & 3) {
+        case 0: out[terms[j]] = re; break;
+        case 1: out[terms[j]] = -im; break;
+        case 2: out[terms[j]] = -re; break;
+        default: out[terms[j]] = im; break;
       }
     }
   }

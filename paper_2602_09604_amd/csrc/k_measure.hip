@@ -121,39 +121,31 @@ __device__ __forceinline__ void accumulate(double* acc, const PauliArgs& a, uint
 }
 
 // Apply each thread's own signs (bit t of own), then sum the block's
-// threads in a fixed order into partials[block][t].
-__device__ __forceinline__ void block_partials(const double* acc, uint32_t own, double* __restrict__ partials) {
-  __shared__ double part[kThreads / 64][kTerms];
+// threads in a fixed order into row[t].  `part` is free again after the next
+// call on another buffer.
+using BlockPart = double[kThreads / 64][kTerms];
+template <int TERMS>
+__device__ __forceinline__ void block_partials(const double* acc, uint32_t own, BlockPart& part,
+                                               double* __restrict__ row) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
-  for (int t = 0; t < kTerms; ++t) {
+  for (int t = 0; t < TERMS; ++t) {
     const double r = wave_sum(((own >> t) & 1) ? -acc[t] : acc[t]);
     if (lane == 0) part[w][t] = r;
   }
   __syncthreads();
-  if (threadIdx.x < kTerms) {
+  if (threadIdx.x < TERMS) {
     double v = 0.0;
     for (int x = 0; x < kThreads / 64; ++x) v += part[x][threadIdx.x];
-    partials[(size_t)blockIdx.x * kTerms + threadIdx.x] = v;
+    row[threadIdx.x] = v;
   }
 }
 
-// Thread T of the grid (nth = gridDim.x * kThreads threads, a power of two)
-// owns items x = T + m nth, m = 0, 1, ...  The bits of first_amp(T) and
-// first_amp(m nth) are disjoint, so the sign (-1)^{|i & z_t|} of every pair
-// splits into a per-thread sign and a per-m sign that is the same for every
-// lane; it reaches the sums through wave-uniform coefficients (+-1 or 0:
-// the real-or-imaginary choice and the sign of bit 0 of z_t folded in), in
-// one of the two ways described at accumulate, and the thread's own sign is
-// applied once at the end.  Mode 0 and 1 items are float4 elements
-// (amplitudes 2x, 2x + 1); mode 2 items are quads: the element at i (bit h
-// clear, i even) and the element holding its partners i ^ f and
-// (i + 1) ^ f.  Every thread keeps two items in flight.
 // The sums of several sweeps of a state held in the caches, in one launch:
-// blockIdx.y is the sweep, and each thread walks its items as above.  A sweep
-// by itself is 4 to 8 us of launch and latency at 20 qubits whatever it reads,
-// so an Ising Hamiltonian's 24 sweeps in a launch each, with a column sum
-// behind every one, took 302 us; as three launches and a wait it takes 48.
+// blockIdx.y is the sweep.  A sweep by itself is 4 to 8 us of launch and
+// latency at 20 qubits whatever it reads, so an Ising Hamiltonian's 24 sweeps in
+// a launch each, with a column sum behind every one, took 302 us; as three
+// launches and a wait it takes 42.
 template <int TERMS>
 struct PauliSweeps {
   static constexpr int kMax = 3072 / (8 + 8 * TERMS);  // sweeps in one launch's arguments
@@ -198,70 +190,87 @@ __host__ __device__ inline int pauli_args(PauliArgs& a, int n, uint64_t f, const
   return mode;
 }
 
+// Block b of the walk owns M kThreads consecutive items (M and the number of
+// blocks are powers of two) and its thread u the items T + m kThreads, T = b M
+// kThreads + u, m < M.  The bits of first_amp(T) and first_amp(m kThreads) are
+// disjoint, so the sign (-1)^{|i & z_t|} of every pair
+// splits into a per-thread sign and a per-m sign that is the same for every
+// lane; it reaches the sums through wave-uniform coefficients (+-1 or 0:
+// the real-or-imaginary choice and the sign of bit 0 of z_t folded in), in
+// one of the two ways described at accumulate, and the thread's own sign is
+// applied once at the end.  Mode 0 and 1 items are float4 elements
+// (amplitudes 2x, 2x + 1); mode 2 items are quads: the element at i (bit h
+// clear, i even) and the element holding its partners i ^ f and
+// (i + 1) ^ f.  Every thread keeps two items in flight.
+// `blocks` follows from the state's size alone, and with it the order of every
+// sum: a term rounds the same whatever else the call asks for.  A launch of
+// many sweeps has fewer workgroups per sweep, each walking several blocks.
 template <int MODE, int TERMS>
-__device__ __forceinline__ void pauli_walk(const float4* __restrict__ psi, const PauliArgs& a,
-                                           double* __restrict__ partials) {
+__device__ __forceinline__ void pauli_walk(const float4* __restrict__ psi, const PauliArgs& a, unsigned blocks,
+                                           BlockPart* part, double* __restrict__ partials) {
   constexpr int NV = MODE == 2 ? 4 : 2;
-  double acc[kTerms];
-#pragma unroll
-  for (int t = 0; t < kTerms; ++t) acc[t] = 0.0;
-  const uint64_t nth = (uint64_t)gridDim.x * kThreads;
-  const uint64_t T = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
-  const uint64_t iT = first_amp<MODE>(a, T);
-  const uint64_t i_step = first_amp<MODE>(a, nth);
+  const uint64_t nth = (uint64_t)blocks * kThreads, M = a.items >= nth ? a.items / nth : 1;
+  const uint64_t i_step = first_amp<MODE>(a, kThreads);
   const uint32_t step = sign_bits(a, i_step, TERMS);  // m even: m + 1 flips these
   const bool fodd = a.f & 1;  // the partner of i is the odd amplitude of its element
-  uint32_t last = 0;  // per-m sign bits of the last item added (FLIPS)
-  if (T < a.items) {  // false only past the end of a state of fewer than nth items
-    // the trip count and has1 are the same for every lane, so the four
-    // loads of an iteration issue back to back (a lone last item loads
-    // its own element twice)
-    const uint64_t M = a.items >= nth ? a.items / nth : 1;
-    for (uint64_t m = 0; m < M; m += 2) {
-      const bool has1 = m + 1 < M;
-      const uint64_t im = first_amp<MODE>(a, m * nth);
-      const uint64_t i0 = iT | im, i1 = has1 ? i0 | i_step : i0;
-      const float4 A0 = gld<false>(psi + (i0 >> 1));
-      const float4 A1 = gld<false>(psi + (i1 >> 1));
-      float4 B0 = A0, B1 = A1;
-      if (MODE == 2) {
-        B0 = gld<false>(psi + (((i0 ^ a.f) & ~(uint64_t)1) >> 1));
-        B1 = gld<false>(psi + (((i1 ^ a.f) & ~(uint64_t)1) >> 1));
-      }
-      const uint32_t sig = sign_bits(a, im, TERMS);
-      double v[NV];
-      item_values<MODE>(A0, B0, fodd, v);
-      accumulate<MODE, TERMS>(acc, a, kFlips<MODE> ? sig ^ last : sig, v);
-      last = sig;
-      if (has1) {
-        item_values<MODE>(A1, B1, fodd, v);
-        accumulate<MODE, TERMS>(acc, a, kFlips<MODE> ? step : sig ^ step, v);
-        last = sig ^ step;
+  int buffer = 0;
+  for (unsigned block = blockIdx.x; block < blocks; block += gridDim.x, buffer ^= 1) {
+    double acc[TERMS];
+#pragma unroll
+    for (int t = 0; t < TERMS; ++t) acc[t] = 0.0;
+    const uint64_t T = (uint64_t)block * (kThreads * M) + threadIdx.x;
+    const uint64_t iT = first_amp<MODE>(a, T);
+    uint32_t last = 0;  // per-m sign bits of the last item added (FLIPS)
+    if (T < a.items) {  // false only past the end of a state of fewer than nth items
+      // the trip count and has1 are the same for every lane, so the four
+      // loads of an iteration issue back to back (a lone last item loads
+      // its own element twice)
+      for (uint64_t m = 0; m < M; m += 2) {
+        const bool has1 = m + 1 < M;
+        const uint64_t im = first_amp<MODE>(a, m * kThreads);
+        const uint64_t i0 = iT | im, i1 = has1 ? i0 | i_step : i0;
+        const float4 A0 = gld<false>(psi + (i0 >> 1));
+        const float4 A1 = gld<false>(psi + (i1 >> 1));
+        float4 B0 = A0, B1 = A1;
+        if (MODE == 2) {
+          B0 = gld<false>(psi + (((i0 ^ a.f) & ~(uint64_t)1) >> 1));
+          B1 = gld<false>(psi + (((i1 ^ a.f) & ~(uint64_t)1) >> 1));
+        }
+        const uint32_t sig = sign_bits(a, im, TERMS);
+        double v[NV];
+        item_values<MODE>(A0, B0, fodd, v);
+        accumulate<MODE, TERMS>(acc, a, kFlips<MODE> ? sig ^ last : sig, v);
+        last = sig;
+        if (has1) {
+          item_values<MODE>(A1, B1, fodd, v);
+          accumulate<MODE, TERMS>(acc, a, kFlips<MODE> ? step : sig ^ step, v);
+          last = sig ^ step;
+        }
       }
     }
+    const uint32_t own = sign_bits(a, iT, TERMS) ^ (kFlips<MODE> ? last : 0u);
+    block_partials<TERMS>(acc, own, part[buffer], partials + (size_t)block * kTerms);
   }
-  const uint32_t own = sign_bits(a, iT, TERMS) ^ (kFlips<MODE> ? last : 0u);
-  block_partials(acc, own, partials);
 }
 
 template <int TERMS>
 __global__ __launch_bounds__(kThreads) void k_pauli_sweeps(const float4* __restrict__ psi, int n,
-                                                          const PauliSweeps<TERMS> s, int first,
+                                                          const PauliSweeps<TERMS> s, int first, unsigned blocks,
                                                           double* __restrict__ partials) {
+  __shared__ BlockPart part[2];
   PauliArgs a;
   const int mode = pauli_args<TERMS>(a, n, s.f[blockIdx.y], s.z[blockIdx.y]);
-  double* out = partials + (size_t)(first + blockIdx.y) * gridDim.x * kTerms;
-  if (mode == 0) pauli_walk<0, TERMS>(psi, a, out);
-  else if (mode == 1) pauli_walk<1, TERMS>(psi, a, out);
-  else pauli_walk<2, TERMS>(psi, a, out);
+  double* out = partials + (size_t)(first + blockIdx.y) * blocks * kTerms;
+  if (mode == 0) pauli_walk<0, TERMS>(psi, a, blocks, part, out);
+  else if (mode == 1) pauli_walk<1, TERMS>(psi, a, blocks, part, out);
+  else pauli_walk<2, TERMS>(psi, a, blocks, part, out);
 }
 
 // The same sums on a streamed state, walked the way the sampling chunk sums
 // walk it: wave W of NW takes chunks of R = 2048 consecutive items, W,
 // W + NW, W + 2 NW, ..., each in 32 steps of 64 lanes, two steps in flight
 // (so the waves in flight read a moving window of the state, each its own
-// 32 KiB run; the grid-stride walk above spreads every wave over the whole
-// state).  Item x = c NW R + W R + k 64 + lane splits into disjoint bit
+// 32 KiB run; a grid-stride walk spreads every wave over the whole state).  Item x = c NW R + W R + k 64 + lane splits into disjoint bit
 // fields, so the per-thread part of every sign comes from W R + lane and
 // the wave-uniform part from c NW R + k 64.  Needs items to be a multiple
 // of NW R.
@@ -270,9 +279,10 @@ template <int MODE, int TERMS>
 __global__ __launch_bounds__(kThreads) void k_pauli_chunks(const float4* __restrict__ psi, const PauliArgs a,
                                                           double* __restrict__ partials) {
   constexpr int NV = MODE == 2 ? 4 : 2;
-  double acc[kTerms];
+  __shared__ BlockPart part;
+  double acc[TERMS];
 #pragma unroll
-  for (int t = 0; t < kTerms; ++t) acc[t] = 0.0;
+  for (int t = 0; t < TERMS; ++t) acc[t] = 0.0;
   const uint64_t NW = (uint64_t)gridDim.x * (kThreads / 64);
   const uint64_t W = (uint64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
@@ -302,7 +312,7 @@ __global__ __launch_bounds__(kThreads) void k_pauli_chunks(const float4* __restr
     }
   }
   const uint32_t own = sign_bits(a, iT, TERMS) ^ (kFlips<MODE> ? last : 0u);
-  block_partials(acc, own, partials);
+  block_partials<TERMS>(acc, own, part, partials + (size_t)blockIdx.x * kTerms);
 }
 
 // Column sums of the blocks x width matrix of per-block partials, in a fixed
@@ -331,20 +341,25 @@ __global__ __launch_bounds__(64 * kFinalWaves) void k_column_sums(const double* 
 }
 
 // The Pauli sums of every sweep: workgroup s adds the blocks x kTerms partials
-// of sweep s, 32 rows at a time, in a fixed order.
-__global__ __launch_bounds__(kThreads) void k_pauli_final(const double* __restrict__ partials, int blocks,
-                                                         double* __restrict__ out) {
-  __shared__ double part[kThreads];
+// of sweep s in a fixed order, 128 rows at a time (columns past a sweep's terms
+// hold nothing and reach nothing).
+constexpr int kFinalRows = 128;
+__global__ __launch_bounds__(kFinalRows * kTerms) void k_pauli_final(const double* __restrict__ partials, int blocks,
+                                                                    double* __restrict__ out) {
+  __shared__ double part[kFinalRows * kTerms];
   const double* p = partials + (size_t)blockIdx.x * blocks * kTerms;
   double s = 0.0;
 #pragma unroll 8
-  for (int i = threadIdx.x; i < blocks * kTerms; i += kThreads) s += p[i];
+  for (int i = threadIdx.x; i < blocks * kTerms; i += kFinalRows * kTerms) s += p[i];
   part[threadIdx.x] = s;
   __syncthreads();
-  if (threadIdx.x >= kTerms) return;
+  if (threadIdx.x >= 64) return;  // 8 runs of 16 rows, then across the runs
   double t = 0.0;
-  for (int r = threadIdx.x; r < kThreads; r += kTerms) t += part[r];
-  out[(size_t)blockIdx.x * kTerms + threadIdx.x] = t;
+#pragma unroll
+  for (int r = 0; r < kFinalRows / 8; ++r) t += part[((threadIdx.x >> 3) * (kFinalRows / 8) + r) * kTerms + (threadIdx.x & 7)];
+#pragma unroll
+  for (int o = 8; o < 64; o <<= 1) t += __shfl_xor(t, o, 64);
+  if (threadIdx.x < kTerms) out[(size_t)blockIdx.x * kTerms + threadIdx.x] = t;
 }
 
 // ------------------------------------------------------- marginal probabilities
@@ -653,8 +668,8 @@ namespace {
 // one class of sweeps (all of at most TERMS terms): partials of sweep i at
 // (first + i) * blocks * kTerms
 template <int TERMS>
-void pauli_class(const void* psi, int n, const std::vector<PauliSweep>& sweeps, const std::vector<int>& which,
-                 int first, unsigned blocks, double* partials, hipStream_t st) {
+void pauli_class(const void* psi, int n, const PauliSweep* sweeps, const std::vector<int>& which, int first,
+                 unsigned blocks, unsigned groups, double* partials, hipStream_t st) {
   if (n >= kern::kNtMinQubits) {  // streamed: a launch per sweep, each bound by memory
     for (size_t i = 0; i < which.size(); ++i) {
       PauliArgs a{};
@@ -672,51 +687,70 @@ void pauli_class(const void* psi, int n, const std::vector<PauliSweep>& sweeps, 
       s.f[i] = sweeps[which[i0 + i]].f;
       std::copy(sweeps[which[i0 + i]].z, sweeps[which[i0 + i]].z + TERMS, s.z[i]);
     }
-    hipLaunchKernelGGL(k_pauli_sweeps<TERMS>, dim3(blocks, (unsigned)m), dim3(kThreads), 0, st, (const float4*)psi, n,
-                       s, first + (int)i0, partials);
+    hipLaunchKernelGGL(k_pauli_sweeps<TERMS>, dim3(groups, (unsigned)m), dim3(kThreads), 0, st, (const float4*)psi, n,
+                       s, first + (int)i0, blocks, partials);
   }
 }
 }  // namespace
 
-// Workgroups per sweep.  Streamed states: all that are resident, each wave
-// walking whole chunks.  Cached ones: a power of two (the kernel's split of
-// signs needs it) of at least two items a thread and about 4096 in a launch.
-unsigned pauli_blocks(int n, size_t sweeps) {
+// Blocks of a sweep's walk.  Streamed states: all that are resident, each wave
+// walking whole chunks.  Cached ones: a power of two (the walk's split of signs
+// needs it) of at least 4 items a thread up to 256 blocks, 16 up to 512 and 32
+// beyond: a call of one sweep wants many blocks, one of many sweeps few
+// reductions (us a call of one term / 8 diagonal terms / an Ising
+// Hamiltonian, with 256, 512, 1024 blocks: 22 qubits 24 / 31 / 76, 24 / 29 / 84,
+// 24 / 29 / 89; 24 qubits 45 / 70 / 350, 40 / 51 / 336, 40 / 44 / 356).
+static unsigned pauli_blocks(int n) {
   if (n >= kern::kNtMinQubits) return kMaxBlocks;
   unsigned b = 1;
   const uint64_t items = n > 1 ? (uint64_t)1 << (n - 2) : 1;
-  while (b < (unsigned)kMaxBlocks && (uint64_t)b * 4 * kThreads <= items && b * 2 * sweeps <= 4096) b *= 2;
+  while ((uint64_t)b * 2 * kThreads * (b < 256 ? 4 : b < 512 ? 16 : 32) <= items) b *= 2;
   return b;
 }
+// Sweeps that share the partials' scratch: 8 MiB of it, 256 at most.
+static size_t pauli_group(int n) {
+  return std::min<size_t>(256, ((size_t)8 << 20) / (sizeof(double) * kTerms * pauli_blocks(n)));
+}
 size_t pauli_scratch_bytes(int n, size_t sweeps) {
-  return sizeof(double) * kTerms * sweeps * pauli_blocks(n, sweeps);
+  return sizeof(double) * kTerms * std::min(sweeps, pauli_group(n)) * pauli_blocks(n);
 }
 
 // Sums of every sweep: out[8 w + t] = sum over pairs (or amplitudes) of term t
 // of sweep order[w].  `order` receives the sweeps' order.
 void launch_pauli(const void* psi, int n, const std::vector<PauliSweep>& sweeps, std::vector<int>& order,
                   double* scratch, double* out, hipStream_t st) {
-  const unsigned blocks = pauli_blocks(n, sweeps.size());
   if (n < 1) throw DeviceError{hipErrorInvalidValue, "k_pauli: n"};
-  std::vector<int> cls[4];
-  for (size_t w = 0; w < sweeps.size(); ++w) {
-    const PauliSweep& s = sweeps[w];
-    if (s.terms < 1 || s.terms > kTerms) throw DeviceError{hipErrorInvalidValue, "k_pauli: 1..8 terms per sweep"};
-    if (n < 64 && (s.f >> n) != 0) throw DeviceError{hipErrorInvalidValue, "k_pauli: flip mask past n"};
-    cls[s.terms <= 1 ? 0 : s.terms <= 2 ? 1 : s.terms <= 4 ? 2 : 3].push_back((int)w);
-  }
+  const unsigned blocks = pauli_blocks(n);
   order.clear();
-  int first = 0;
-  for (int c = 0; c < 4; ++c) {
-    if (c == 0) pauli_class<1>(psi, n, sweeps, cls[c], first, blocks, scratch, st);
-    else if (c == 1) pauli_class<2>(psi, n, sweeps, cls[c], first, blocks, scratch, st);
-    else if (c == 2) pauli_class<4>(psi, n, sweeps, cls[c], first, blocks, scratch, st);
-    else pauli_class<8>(psi, n, sweeps, cls[c], first, blocks, scratch, st);
-    order.insert(order.end(), cls[c].begin(), cls[c].end());
-    first += (int)cls[c].size();
+  for (size_t w0 = 0; w0 < sweeps.size(); w0 += pauli_group(n)) {
+    const size_t count = std::min(pauli_group(n), sweeps.size() - w0);
+    // Workgroups of a launch of several sweeps: up to 22 qubits the state stays
+    // in the L2s whatever the order; above, sweeps that are resident together
+    // read the same part of it at the same time (24 masks at 24 qubits: 336 us
+    // with 4096 workgroups, 446 with 8192; 22 masks at 22: 86 and 75).
+    const size_t resident = n <= 22 ? 8192 : 4096;
+    unsigned groups = blocks;
+    while (n < kern::kNtMinQubits && groups > 1 && groups * count > resident) groups /= 2;
+    std::vector<int> cls[4];
+    for (size_t w = 0; w < count; ++w) {
+      const PauliSweep& s = sweeps[w0 + w];
+      if (s.terms < 1 || s.terms > kTerms) throw DeviceError{hipErrorInvalidValue, "k_pauli: 1..8 terms per sweep"};
+      if (n < 64 && (s.f >> n) != 0) throw DeviceError{hipErrorInvalidValue, "k_pauli: flip mask past n"};
+      cls[s.terms <= 1 ? 0 : s.terms <= 2 ? 1 : s.terms <= 4 ? 2 : 3].push_back((int)w);
+    }
+    int first = 0;
+    for (int c = 0; c < 4; ++c) {
+      const PauliSweep* g = sweeps.data() + w0;
+      if (c == 0) pauli_class<1>(psi, n, g, cls[c], first, blocks, groups, scratch, st);
+      else if (c == 1) pauli_class<2>(psi, n, g, cls[c], first, blocks, groups, scratch, st);
+      else if (c == 2) pauli_class<4>(psi, n, g, cls[c], first, blocks, groups, scratch, st);
+      else pauli_class<8>(psi, n, g, cls[c], first, blocks, groups, scratch, st);
+      for (int w : cls[c]) order.push_back((int)w0 + w);
+      first += (int)cls[c].size();
+    }
+    hipLaunchKernelGGL(k_pauli_final, dim3((unsigned)count), dim3(kFinalRows * kTerms), 0, st, (const double*)scratch,
+                       (int)blocks, out + kTerms * w0);
   }
-  hipLaunchKernelGGL(k_pauli_final, dim3((unsigned)sweeps.size()), dim3(kThreads), 0, st, (const double*)scratch,
-                     (int)blocks, out);
   SV_HIP(hipGetLastError());
 }
 

@@ -232,7 +232,6 @@ struct PauliSweep {
   int terms = 0;
   uint64_t z[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 };
-constexpr size_t kPauliSweepsMax = 256;  // sweeps per call of launch_pauli
 size_t pauli_scratch_bytes(int n, size_t sweeps);
 void launch_pauli(const void* psi, int n, const std::vector<PauliSweep>& sweeps, std::vector<int>& order,
                   double* scratch, double* out, hipStream_t st);
