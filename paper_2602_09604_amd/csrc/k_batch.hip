@@ -317,7 +317,10 @@ BatchOut batch_run_impl(sv_state* const* states, const int* ns, const sv_gate* c
   const size_t off_pass = al(off_circ + sizeof(BCirc) * alone.size());
   const size_t off_mat = al(off_pass + sizeof(BPass) * passes.size());
   const size_t total = al(off_mat + sizeof(float) * mats.size());
-  if (levels.empty() && alone.empty()) return out;
+  if (levels.empty() && alone.empty()) {  // nothing to launch, but the handles' queued work is waited for
+    SV_HIP(hipStreamSynchronize(state_stream(states[0])));
+    return out;
+  }
   unsigned char *host = nullptr, *dev = nullptr;
   state_staging(states[0], total, &host, &dev);
   for_circuits(n_circ, [&](size_t c) {
