@@ -333,8 +333,10 @@ int sv_write_amplitudes(sv_state* s, uint64_t start, uint64_t count, const float
  * first per opts (fusion mode and max_k; GREEDY with max_k 4 when opts is
  * NULL; the precision is always FP32), circuits on host threads.  A controlled gate wider than max_k with its controls is
  * rejected (SV_EINVAL).  States of at most 30 qubits.  When stats is not NULL
- * the call waits and fills it.  Equivalent to sv_apply_circuit on each state
- * in turn. */
+ * the call waits and fills it.  Pass data is staged with states[0], which
+ * keeps up to 64 MiB of pinned host memory and as much on the device for it;
+ * what a call needed beyond that is given back.  Equivalent to
+ * sv_apply_circuit on each state in turn. */
 int sv_batch_run(sv_state* const* states, const sv_gate* const* circuits, const size_t* n_gates,
                  size_t n_circuits, const sv_run_opts* opts, sv_run_stats* stats);
 

@@ -1096,6 +1096,16 @@ void state_staging(sv_state* s, size_t bytes, unsigned char** host, unsigned cha
   *host = s->arena_host + at;
   *dev = s->arena_dev + at;
 }
+// Gives the ring back if it has grown past `keep` bytes.  The handle's stream
+// holds no work that uses it.
+void state_staging_trim(sv_state* s, size_t keep) {
+  if (s->arena_cap <= keep) return;
+  s->arena_cap = s->ring_pos = 0;
+  unsigned char *dev = s->arena_dev, *host = s->arena_host;
+  s->arena_dev = s->arena_host = nullptr;
+  SV_HIP(hipFree(dev));
+  SV_HIP(hipHostFree(host));
+}
 // After a batched run: a circuit with a gate that is not unitary leaves the
 // state's norm unknown to the host.
 void state_note_gates(sv_state* s, const sv_gate* g, size_t n) {

@@ -31,6 +31,7 @@ hipStream_t state_stream(sv_state* s);
 bool state_poisoned(sv_state* s);
 void state_poison(sv_state* s);
 void state_staging(sv_state* s, size_t bytes, unsigned char** host, unsigned char** dev);
+void state_staging_trim(sv_state* s, size_t keep);
 void state_note_gates(sv_state* s, const sv_gate* g, size_t n);
 
 namespace {
@@ -127,6 +128,9 @@ constexpr int kBatchLdsMaxQubits = 14;
 constexpr int kBatchTileBits = 12;
 constexpr int kBatchAloneQubits = 9;     // circuits k_batch_lds may run
 constexpr uint64_t kBatchGroups = 256;   // workgroups per state in a launch
+// Staging that stays with the first handle: 512 circuits of 10 to 22 qubits take
+// a ring of 64 MiB, which costs about 1 ms to allocate anew.
+constexpr size_t kBatchKeepBytes = (size_t)64 << 20;
 
 void fill_pass(BPass& bp, int n, const FusedGate& f, uint32_t mat) {
   int pos[SV_MAX_K];
@@ -367,6 +371,7 @@ BatchOut batch_run_impl(sv_state* const* states, const int* ns, const sv_gate* c
   float ms = 0.f;
   SV_HIP(hipEventElapsedTime(&ms, e0, e1));
   out.gpu_s = ms * 1e-3;
+  state_staging_trim(states[0], kBatchKeepBytes);
   return out;
 }
 }  // namespace
