@@ -1088,6 +1088,7 @@ namespace sv {
 void* state_psi(sv_state* s) { return s->psi; }
 int state_n(sv_state* s) { return s->n; }
 hipStream_t state_stream(sv_state* s) { return s->stream; }
+int state_device(sv_state* s) { return s->device; }
 bool state_poisoned(sv_state* s) { return s->poisoned; }
 void state_poison(sv_state* s) { s->poisoned = true; }
 // `bytes` of the handle's staging ring: pinned host memory and its device copy.

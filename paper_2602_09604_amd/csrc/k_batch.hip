@@ -28,6 +28,7 @@ namespace sv {
 void* state_psi(sv_state* s);
 int state_n(sv_state* s);
 hipStream_t state_stream(sv_state* s);
+int state_device(sv_state* s);
 bool state_poisoned(sv_state* s);
 void state_poison(sv_state* s);
 void state_staging(sv_state* s, size_t bytes, unsigned char** host, unsigned char** dev);
@@ -407,6 +408,7 @@ extern "C" int sv_batch_run(sv_state* const* states, const sv_gate* const* circu
   o.precision = SV_PREC_FP32_VALU;
   std::vector<hipEvent_t> waits;
   try {
+    SV_HIP(hipSetDevice(state_device(states[0])));  // its staging ring outlives the call
     // work already queued on the other handles' streams (initialisation,
     // earlier passes) must finish before the batch touches their states
     const hipStream_t st0 = state_stream(states[0]);
