@@ -344,7 +344,11 @@ int sv_batch_run(sv_state* const* states, const sv_gate* const* circuits, const 
 
 /* Time the candidate tile shapes of every kernel variant on a scratch state
  * of n qubits on the handle's device (the handle's state is overwritten) and
- * keep the fastest per (variant, k, lowest-target bucket, precision).
+ * keep the fastest per (variant, k, lowest-target bucket, precision).  The
+ * table decides the kernel of a pass that is launched by itself (with k >= 5
+ * too, where the untuned choice may be a tile sweep of one pass; a class for which
+ * the untuned choice is the fastest gets no entry); passes that share a tile
+ * sweep are not looked up.
  * Results persist across calls in this process; sv_tune_save/sv_tune_load
  * write and read them as JSON. */
 int sv_autotune(sv_state* s, int budget_ms);

@@ -285,6 +285,7 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
       continue;
     }
     p.variant = choose_variant(s->n, p.k, p.s, o.precision, o.variant == SV_VARIANT_SHFL ? V_SHFL : o.variant);
+    p.tuned = tuned_variant(s->n, p.k, p.s, o.precision) == p.variant;
     // passes the split matrix cores do not take (k = 5, 6 on states below k + 6
     // qubits, or by the tuned table) run in FP32, in a sweep too
     if (p.k >= 4 && p.variant != V_MFMA) p.precision = SV_PREC_FP32_VALU;
@@ -329,11 +330,14 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
   }
   size_t total = 0;
   for (Launch& l : launches) {
-    if (l.sweep.T && (l.sweep.members.size() > 1 || sweep_alone(s->n, passes[l.sweep.members[0]].k, passes[l.sweep.members[0]].precision))) {
+    const Pass& p0 = passes[l.sweep.members[0]];
+    // a pass that shares its tile with no other takes the kernel the tuned
+    // table names for it
+    if (l.sweep.T && (l.sweep.members.size() > 1 || (!p0.tuned && sweep_alone(s->n, p0.k, p0.precision)))) {
       l.bytes = l.sweep.data_bytes;
     } else {
       l.sweep.T = 0;
-      l.bytes = passes[l.sweep.members[0]].mat_bytes;
+      l.bytes = p0.mat_bytes;
     }
     l.off = total;
     total += align256(l.bytes);

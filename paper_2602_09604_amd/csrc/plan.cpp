@@ -66,7 +66,20 @@ static bool lds_feasible(int n, int k, const int* s, int tile_bits) {
   return n >= 8 && k <= SV_MAX_K;
 }
 
-int tuned_variant(int n, int k, const int* s, int precision);
+// AUTO without a tuned entry, from sweeps at 30 and 32 qubits: matrix cores for
+// k >= 4 when the precision asks for them; the wavefront shuffle for k <= 2 with
+// every target in bits 0..6; on streamed states the register kernel
+// whenever it reads whole lines (its lane exchange covers targets on bits
+// 1..3): 0.68-0.76 of peak against 0.49-0.65 for LDS staging on every
+// low-target set measured; LDS staging for other low targets up to k = 4.
+int untuned_variant(int n, int k, const int* s, int precision) {
+  if (precision != SV_PREC_FP32_VALU && mfma_supported(k, precision) && n >= k + 6) return V_MFMA;
+  if (shfl_eligible(n, k, s) && k <= 2) return V_SHFL;  // at k = 3 the permutes cost more; only when tuned
+  if (reg_streams(n, k, s)) return V_REG;
+  if (has_low_target(k, s) && k <= 4 && lds_feasible(n, k, s, tuned_shape(V_LDS, n, k, s, precision).tile_bits))
+    return V_LDS;
+  return V_REG;
+}
 
 int choose_variant(int n, int k, const int* s, int precision, int requested) {
   const Shape sh = tuned_shape(V_LDS, n, k, s, precision);
@@ -82,17 +95,7 @@ int choose_variant(int n, int k, const int* s, int precision, int requested) {
   if (tv == V_MFMA && mfma_ok) return V_MFMA;
   if (tv == V_LDS && lds_feasible(n, k, s, sh.tile_bits)) return V_LDS;
   if (tv == V_REG) return V_REG;
-  // untuned defaults, from sweeps at 30 and 32 qubits: matrix cores for k >= 4
-  // when the precision asks for them; the wavefront shuffle for k <= 2 with
-  // every target in bits 0..6; on streamed states the register kernel
-  // whenever it reads whole lines (its lane exchange covers targets on bits
-  // 1..3): 0.68-0.76 of peak against 0.49-0.65 for LDS staging on every
-  // low-target set measured; LDS staging for other low targets up to k = 4
-  if (precision != SV_PREC_FP32_VALU && mfma_ok) return V_MFMA;
-  if (shfl_ok && k <= 2) return V_SHFL;  // at k = 3 the permutes cost more; only when tuned
-  if (reg_streams(n, k, s)) return V_REG;
-  if (has_low_target(k, s) && k <= 4 && lds_feasible(n, k, s, sh.tile_bits)) return V_LDS;
-  return V_REG;
+  return untuned_variant(n, k, s, precision);
 }
 
 }  // namespace sv

@@ -57,6 +57,7 @@ struct Pass {
   int s[SV_MAX_K] = {0, 0, 0, 0, 0, 0};  // sorted targets
   int variant = V_REG;                   // resolved (never AUTO)
   int precision = SV_PREC_FP32_VALU;
+  bool tuned = false;                    // the variant is the tuned table's
   size_t mat_bytes = 0;                  // bytes of the pass data
   // launch shape (from the tuner or defaults)
   int tile_bits = 13;                    // LDS: log2 amplitudes per tile
@@ -121,6 +122,8 @@ bool mfma_ctrl_supported(int n, int k, uint64_t cmask);
 void normalise_gate(int k, const int32_t* qubits, const double* mat, int* sorted_out,
                     std::vector<double>& mat_out);
 int choose_variant(int n, int k, const int* s, int precision, int requested);
+int untuned_variant(int n, int k, const int* s, int precision);
+int tuned_variant(int n, int k, const int* s, int precision);  // -1: no entry
 Shape tuned_shape(int variant, int n, int k, const int* s, int precision);
 int lds_split(int tile_bits, int k, const int* s, int* m_out);
 int lds_tile_bits_for(int n, int want);

@@ -6,6 +6,9 @@
 // the contiguous wavefront rows), the LDS tile split, and whether a matrix-core
 // variant applies.  Candidates: the register kernel, the LDS kernel with 2^10
 // and 2^12 amplitude tiles, and the MFMA kernel for k >= 4 in MFMA precisions.
+// From k = 5 a pass by itself may also be a tile sweep.  The table has no entry
+// for that, and its classes do not know the size of the state the sweep's rule
+// goes by, so a class whose fastest kernel is the untuned choice is left out of it.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -19,6 +22,7 @@
 #include <tuple>
 
 #include "sv_internal.h"
+#include "sweep.h"
 
 namespace sv {
 
@@ -108,6 +112,7 @@ int sv_autotune(sv_state* s, int budget_ms) {
     std::mt19937_64 rng(12345);
     std::normal_distribution<double> nd;
     std::map<Key, Choice> found;
+    std::vector<Key> untuned;  // classes that are to have no entry
     const int precs[4] = {SV_PREC_FP32_VALU, SV_PREC_FP32_MFMA, SV_PREC_BF16X3, SV_PREC_FP16X3};
     for (int pi = 0; pi < 4; ++pi) {
       const int prec = precs[pi];
@@ -131,18 +136,13 @@ int sv_autotune(sv_state* s, int budget_ms) {
             if (mfma_supported(k, prec) && n >= k + 6) cands.push_back({V_MFMA, 12});
             if (shfl_eligible(n, k, p.s)) cands.push_back({V_SHFL, 12});
             Choice best{V_REG, 12, 1e30};
-            for (auto& cand : cands) {
-              p.variant = cand.first;
-              p.tile_bits = cand.second;
-              p.mfma_x = p.variant == V_MFMA ? mfma_exchange_mask(n, p) : 0;
-              p.mat_bytes = pass_data_bytes(p);
-              encode_pass_data(p, mat.data(), host);
-              SV_HIP(hipMemcpyAsync(dev, host, p.mat_bytes, hipMemcpyHostToDevice, st));
-              launch_pass(p, n, psi, dev, st);  // warm-up
+            auto time_of = [&](size_t bytes, auto&& launch) {
+              SV_HIP(hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, st));
+              launch();  // warm-up
               std::vector<float> t;
               for (int r = 0; r < 3; ++r) {
                 SV_HIP(hipEventRecord(e0, st));
-                launch_pass(p, n, psi, dev, st);
+                launch();
                 SV_HIP(hipEventRecord(e1, st));
                 SV_HIP(hipEventSynchronize(e1));
                 float ms = 0.f;
@@ -150,11 +150,36 @@ int sv_autotune(sv_state* s, int budget_ms) {
                 t.push_back(ms);
               }
               std::sort(t.begin(), t.end());
-              if (t[1] < best.ms) best = Choice{cand.first, cand.second, t[1]};
               // renormalise occasionally: random matrices grow the state
               launch_init_basis(psi, n, 0, st);
+              return t[1];
+            };
+            for (auto& cand : cands) {
+              p.variant = cand.first;
+              p.tile_bits = cand.second;
+              p.mfma_x = p.variant == V_MFMA ? mfma_exchange_mask(n, p) : 0;
+              p.mat_bytes = pass_data_bytes(p);
+              encode_pass_data(p, mat.data(), host);
+              const float ms = time_of(p.mat_bytes, [&] { launch_pass(p, n, psi, dev, st); });
+              if (ms < best.ms) best = Choice{cand.first, cand.second, ms};
             }
-            found[key_of(prec, k, p.s)] = best;
+            bool by_rule = false;  // the untuned choice is the fastest
+            if (k >= 5) {
+              const int T = sweep_tile_bits(n, prec);
+              if (sweep_alone(n, k, prec) && sweep_kind(T, k, prec)) {
+                std::vector<SweepItem> item(1);
+                for (int j = 0; j < k; ++j) item[0].mask |= (uint64_t)1 << p.s[j];
+                item[0].kind = sweep_kind(T, k, prec);
+                std::vector<Sweep> plan;
+                plan_sweeps(item, n, T, sweep_mat_room(n, T, prec), prec, plan);
+                encode_sweep(plan[0], {&p}, {mat.data()}, host);
+                by_rule = time_of(plan[0].data_bytes, [&] { launch_sweep(plan[0], n, psi, dev, st); }) <= best.ms;
+              } else {
+                by_rule = best.variant == untuned_variant(n, k, p.s, prec);
+              }
+            }
+            if (by_rule) untuned.push_back(key_of(prec, k, p.s));
+            else found[key_of(prec, k, p.s)] = best;
             if (budget_ms > 0 &&
                 std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_start).count() >
                     budget_ms)
@@ -169,6 +194,7 @@ int sv_autotune(sv_state* s, int budget_ms) {
     {
       std::lock_guard<std::mutex> lk(g_mu);
       for (auto& kv : found) g_table[kv.first] = kv.second;
+      for (auto& key : untuned) g_table.erase(key);
     }
     bump_plan_epoch();
     (void)hipFree(dev);
