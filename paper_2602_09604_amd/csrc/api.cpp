@@ -333,7 +333,7 @@ static void run_passes(sv_state* s, const std::vector<FusedGate>& fused, const s
     const Pass& p0 = passes[l.sweep.members[0]];
     // a pass that shares its tile with no other takes the kernel the tuned
     // table names for it
-    if (l.sweep.T && (l.sweep.members.size() > 1 || (!p0.tuned && sweep_alone(s->n, p0.k, p0.precision)))) {
+    if (l.sweep.T && (l.sweep.members.size() > 1 || (!p0.tuned && sweep_alone(s->n, p0.k, p0.s, p0.precision, graph)))) {
       l.bytes = l.sweep.data_bytes;
     } else {
       l.sweep.T = 0;

@@ -40,14 +40,34 @@ int sweep_kind(int T, int k, int precision) {
   return op_kind(k, precision);
 }
 
-// FP32: from k = 5, where the register kernel is bound by its ALUs (one
-// 5-qubit gate at 28 qubits 1060-1612 us there, 774-820 us here; 12 to 20
-// qubits 70-80 us there, 24 here) and the FP32 pass of k_mfma.hip by its
-// larger instructions (793-892 us; 6 qubits 1440-1556 against 1502); at k = 4
-// the pass kernels are as fast. Split precisions: up to 20 qubits (5 qubits 36
-// -> 30 us in FP16X3); above, k_mfma.hip's passes stream better (28 qubits 711
-// against 892 us).
-bool sweep_alone(int n, int k, int precision) { return k >= 5 && (!split_precision(precision) || n <= 20); }
+// From k = 5; at k = 4 the pass kernels are as fast.
+// FP32_VALU: the register kernel is bound by its ALUs there (5 qubits, 12 to 20
+// qubits of state: 60-72 us, here 12-15; 24: 104, 65; 26: 241-414, 197-271; 6
+// qubits, 24 qubits of state: 214-366, 118-132).  At k = 5 its 3M form streams
+// as fast in the end: with bit 0 and no target in bits 1..3, where its
+// elements are halves of groups, from 28 qubits (760-822 us against 875-1086;
+// 30 qubits: 3.1-3.4 ms against 4.5-4.9, since a tile with few long rows far
+// apart reads memory more slowly), and for any targets from 32 (12.4-16.0 ms
+// against 11.8-16.9, 0.6 % apart on average; at 30 the sweep is 8 % faster).
+// FP32_MFMA: the pass of k_mfma.hip from 21 qubits (22 qubits: 23-28 us against 28
+// at k = 5, 35-41 against 46 at k = 6; 6 qubits, 28 qubits of state: 1.30-1.59 ms
+// against 1.50, 32: 17.9-20.9 against 23.5), except 5-qubit passes on bit 0 and
+// bits 1..3 of a streamed state, where it exchanges lanes (26 and 28 qubits:
+// 0.68-0.96 of its time here), and except 6-qubit passes below 24 qubits that
+// are encoded for the call: a call of them is bound by the host, which writes
+// 64 KiB for a pass there and 32 here (21 / 22 / 23 qubits of quantum volume at
+// depth 10: 1.69 / 1.83 / 2.02 ms a call there, 1.44 / 1.60 / 1.81 here; as a kept
+// graph 0.57 against 0.81 at 22).
+// Split precisions: up to 20 qubits (6 qubits: 18.4-23.8 us there, 14.5-17.7 here;
+// 5 qubits 10.4-14.6, 11.0-14.7); above, k_mfma.hip's passes stream better (28
+// qubits 711 against 892 us).
+bool sweep_alone(int n, int k, const int* s, int precision, bool graph) {
+  if (k < 5) return false;
+  if (split_precision(precision)) return n <= 20;
+  const bool low = s[0] == 0 && s[1] <= 3;  // bit 0 and one of bits 1..3
+  if (precision == SV_PREC_FP32_MFMA && n > 20) return k == 5 ? low && n >= 26 : n < 24 && !graph;
+  return k >= 6 || (n < 32 && (n < 28 || s[0] != 0 || low));
+}
 
 // Greedy in passes: a sweep is seeded with the first pass left and takes
 // every later eligible pass whose targets still fit in the tile and which

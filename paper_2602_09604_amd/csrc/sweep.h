@@ -86,8 +86,9 @@ struct SweepItem {
 int sweep_tile_bits(int n, int precision);
 // Device kind of a k-target pass in a sweep with tiles of T bits; 0: it does not run in one.
 int sweep_kind(int T, int k, int precision);
-// Whether a pass that shares its sweep with no other still runs as one.
-bool sweep_alone(int n, int k, int precision);
+// Whether a pass (sorted targets) that shares its sweep with no other still runs
+// as one; graph: its data may be on the device from an earlier call.
+bool sweep_alone(int n, int k, const int* s, int precision, bool graph);
 // T: tile size, at most n; mat_room: LDS bytes for the matrices of a sweep.
 void plan_sweeps(const std::vector<SweepItem>& items, int n, int T, size_t mat_room, int precision,
                  std::vector<Sweep>& out);

@@ -166,7 +166,7 @@ int sv_autotune(sv_state* s, int budget_ms) {
             bool by_rule = false;  // the untuned choice is the fastest
             if (k >= 5) {
               const int T = sweep_tile_bits(n, prec);
-              if (sweep_alone(n, k, prec) && sweep_kind(T, k, prec)) {
+              if (sweep_alone(n, k, p.s, prec, true) && sweep_kind(T, k, prec)) {
                 std::vector<SweepItem> item(1);
                 for (int j = 0; j < k; ++j) item[0].mask |= (uint64_t)1 << p.s[j];
                 item[0].kind = sweep_kind(T, k, prec);
