@@ -442,18 +442,31 @@ int sv_mlp_forward(sv_mlp* m, const float* x_dev, int batch, float* y_dev) {
   MLP_GUARD_END
 }
 
+// Room for the partials of a batch of `batch` samples.  Without it the network
+// is as it was, and calls with smaller batches go on.
+static void mlp_reserve(sv_mlp* m, int batch) {
+  const int blocks = (batch + CH - 1) / CH;
+  if (blocks <= m->max_blocks) return;
+  SV_HIP(hipStreamSynchronize(m->stream));
+  float* old = m->partial;
+  m->partial = nullptr;
+  m->max_blocks = 0;
+  if (old) SV_HIP(hipFree(old));
+  const hipError_t e = hipMalloc(&m->partial, sizeof(float) * (size_t)(m->nparams + 1) * blocks);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();  // reported here, not by the next launch
+    m->partial = nullptr;
+    throw DeviceError{e, "hipMalloc of the gradient partials"};
+  }
+  m->max_blocks = blocks;
+}
+
 // `adam`: also update the parameters with this gradient
 static void mlp_loss_grad_async(sv_mlp* m, const float* x_dev, const float* y_dev, int batch,
                                 const AdamArgs* adam = nullptr) {
   const int blocks = (batch + CH - 1) / CH;
   const int stride = m->nparams + 1;
-  if (blocks > m->max_blocks) {
-    SV_HIP(hipStreamSynchronize(m->stream));
-    if (m->partial) SV_HIP(hipFree(m->partial));
-    m->partial = nullptr;
-    SV_HIP(hipMalloc(&m->partial, sizeof(float) * (size_t)stride * blocks));
-    m->max_blocks = blocks;
-  }
+  mlp_reserve(m, batch);
   hipLaunchKernelGGL(k_mlp_grad<64>, dim3(blocks, 2), dim3(1024), 0, m->stream, m->params, x_dev, y_dev, batch,
                      m->partial, stride);
   SV_HIP(hipGetLastError());
