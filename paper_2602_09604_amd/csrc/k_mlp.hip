@@ -513,6 +513,7 @@ int sv_mlp_adam_step(sv_mlp* m, float lr, float beta1, float beta2, float eps) {
 int sv_mlp_train(sv_mlp* m, const float* x_dev, const float* y_dev, int n, int epochs, float lr, float* final_loss) {
   if (!m || !x_dev || !y_dev || n < 1 || epochs < 1 || !(lr > 0)) return fail(SV_EINVAL, "bad arguments");
   MLP_GUARD_BEGIN
+  mlp_reserve(m, n);  // before the first step is counted
   for (int e = 0; e < epochs; ++e) {
     const AdamArgs adam = mlp_adam_next(m, lr, 0.9f, 0.999f, 1e-8f);
     mlp_loss_grad_async(m, x_dev, y_dev, n, &adam);

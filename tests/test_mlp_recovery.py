@@ -38,3 +38,17 @@ def test_smaller_batch_after_a_failed_one():
     finally:
         a.free()
         b.free()
+
+
+def test_a_failed_call_counts_no_step():
+    """Adam's bias corrections go by the number of updates made."""
+    sv, x, y = make(100)
+    a, b = sv.Mlp(seed=2), sv.Mlp(seed=2)
+    try:
+        too_large(sv, a, x, y)
+        for m in (a, b):
+            m.train(x, y, epochs=3, lr=3e-3)
+        assert np.array_equal(a.get_params(), b.get_params())
+    finally:
+        a.free()
+        b.free()
