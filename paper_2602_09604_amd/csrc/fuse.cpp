@@ -24,6 +24,7 @@
 #include <condition_variable>
 #include <cstring>
 #include <exception>
+#include <limits>
 #include <functional>
 #include <memory>
 #include <mutex>
@@ -121,7 +122,7 @@ void lower_controlled(const sv_gate* g, size_t n, int max_k, std::vector<sv_gate
 // (local bit j of G = block bit pos[j]).  The rows of M that differ only in
 // G's bits are combined whole, so the inner loop runs over contiguous columns.
 // `skip`: leave out products with zero entries (most of a diagonal or
-// permutation gate); only for blocks without infinities and NaNs.
+// permutation gate); only where they add nothing (ZeroSkip).
 static void left_multiply(std::vector<double>& Mr, std::vector<double>& Mi, int K, const sv_gate& g,
                           const int* pos, bool skip) {
   const int d = 1 << K, k = g.k, dk = 1 << k;
@@ -166,12 +167,36 @@ static void left_multiply(std::vector<double>& Mr, std::vector<double>& Mi, int 
   }
 }
 
-static bool all_finite(const sv_gate* g, const std::vector<int>& members) {
-  for (int i : members)
-    for (size_t e = 0; e < ((size_t)2 << (2 * g[i].k)); ++e)
-      if (!std::isfinite(g[i].matrix[e])) return false;
-  return true;
+// Largest sum of |re| + |im| over a row of the gate, at least 1; infinite for a NaN.
+static double row_growth(const sv_gate& g) {
+  constexpr double kInf = std::numeric_limits<double>::infinity();
+  const size_t row = (size_t)2 << g.k, all = row << g.k;
+  double most = 1.0;
+  for (size_t e = 0; e < all; e += row) {
+    double s = 0.0;
+    for (size_t c = 0; c < row; ++c) s += std::fabs(g.matrix[e + c]);
+    if (!(s <= most)) most = s < kInf ? s : kInf;
+  }
+  return most;
 }
+
+// Whether the next gate's zero entries may be left out of a block's product: as
+// long as every entry of the block, and every sum on the way, stays finite.
+// `bound` holds the block's largest |re| or |im|; it grows by each gate's
+// row_growth and is taken from the block again before it gets near overflow.
+struct ZeroSkip {
+  double bound = 1.0;
+  bool next(double growth, const std::vector<double>& Mr, const std::vector<double>& Mi) {
+    constexpr double kInf = std::numeric_limits<double>::infinity();
+    if (bound < kInf && !(bound * growth < 1e150)) {
+      double m = 0.0;
+      for (size_t e = 0; e < Mr.size(); ++e) m = std::max(m, std::max(std::fabs(Mr[e]), std::fabs(Mi[e])));
+      bound = m;
+    }
+    bound = bound * growth < 1e300 ? bound * growth : kInf;
+    return bound < kInf;
+  }
+};
 
 // Build the fused gate of an ordered member list.
 static void build_block(const sv_gate* g, const std::vector<int>& members, FusedGate& out) {
@@ -196,11 +221,11 @@ static void build_block(const sv_gate* g, const std::vector<int>& members, Fused
   const int d = 1 << K;
   std::vector<double> Mr((size_t)d * d, 0.0), Mi((size_t)d * d, 0.0);
   for (int i = 0; i < d; ++i) Mr[(size_t)i * d + i] = 1.0;
-  const bool skip = all_finite(g, members);
+  ZeroSkip skip;
   for (int i : members) {
     int pos[SV_MAX_K];
     for (int j = 0; j < g[i].k; ++j) pos[j] = bitpos[g[i].qubits[j]];
-    left_multiply(Mr, Mi, K, g[i], pos, skip);
+    left_multiply(Mr, Mi, K, g[i], pos, skip.next(row_growth(g[i]), Mr, Mi));
   }
   out.mat.resize((size_t)2 * d * d);
   for (size_t i = 0; i < (size_t)d * d; ++i) {
@@ -261,7 +286,8 @@ static void build_block_mux(const sv_gate* g, const std::vector<int>& members, i
   }
   const int d = 1 << K;
   std::vector<double> Mr, Mi, dmat;
-  const bool skip = all_finite(g, members);
+  std::vector<double> growth;
+  for (int i : members) growth.push_back(row_growth(g[i]));
   for (int v = 0; v < (1 << nc); ++v) {
     uint64_t cval = 0;
     for (int t = 0; t < nc; ++t)
@@ -269,8 +295,10 @@ static void build_block_mux(const sv_gate* g, const std::vector<int>& members, i
     Mr.assign((size_t)d * d, 0.0);
     Mi.assign((size_t)d * d, 0.0);
     for (int i = 0; i < d; ++i) Mr[(size_t)i * d + i] = 1.0;
-    for (int i : members) {
-      const sv_gate& h = g[i];
+    ZeroSkip zeros;
+    for (size_t at = 0; at < members.size(); ++at) {
+      const sv_gate& h = g[members[at]];
+      const bool skip = zeros.next(growth[at], Mr, Mi);
       int pos[SV_MAX_K];
       if ((qmask(h) & Cm) == 0) {
         for (int j = 0; j < h.k; ++j) pos[j] = bitpos[h.qubits[j]];
