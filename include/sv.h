@@ -153,10 +153,11 @@ typedef struct {
 typedef struct {
   uint64_t gates_in;     /* gates given */
   uint64_t passes;       /* fused passes applied */
-  uint64_t bytes;        /* algorithmic HBM bytes: 16 * 2^n per pass, 16 * 2^(n-c)
-                            for a controlled pass with c controls; for sv_batch_run
-                            16 * 2^n per LDS-resident circuit (one read, one write)
-                            plus 16 * 2^n per pass of every other circuit */
+  uint64_t bytes;        /* bytes of the passes one by one: 16 * 2^n per pass, 16 * 2^(n-c)
+                            for a controlled pass with c controls (sv_batch_run: of every
+                            circuit).  Passes that share a tile sweep move the state once:
+                            the launches of an sv_apply_circuit move
+                            bytes - (passes - launches) * 16 * 2^n */
   double useful_flops;   /* sum over passes of groups * 2^k (8*2^k - 2), groups =
                             2^(n-k) (2^(n-k-c) for a controlled pass) */
   double fuse_s;         /* host time in the fusion pass */

@@ -16,7 +16,6 @@
 #include <exception>
 #include <thread>
 #include <cstring>
-#include <mutex>
 
 #include <stdexcept>
 
@@ -123,9 +122,6 @@ bool shape_supported(int mode, int K) {
   return (mode == 0 && K >= 1 && K <= 5) || (mode == 1 && K >= 0 && K <= 5) || (mode == 2 && K == 6);
 }
 
-std::mutex g_batch_mu;
-int g_lds_max_n = 12;  // largest LDS-resident state (qubits); set by the autotuner
-constexpr int kBatchLdsMaxQubits = 14;
 constexpr int kBatchTileBits = 12;
 constexpr int kBatchAloneQubits = 9;     // circuits k_batch_lds may run
 constexpr uint64_t kBatchGroups = 256;   // workgroups per state in a launch
@@ -159,15 +155,6 @@ void fill_pass(BPass& bp, int n, const FusedGate& f, uint32_t mat) {
 }
 
 }  // namespace
-
-int batch_lds_max_n() {
-  std::lock_guard<std::mutex> lk(g_batch_mu);
-  return g_lds_max_n;
-}
-void set_batch_lds_max_n(int n) {
-  std::lock_guard<std::mutex> lk(g_batch_mu);
-  g_lds_max_n = std::max(1, std::min(kBatchLdsMaxQubits, n));
-}
 
 int plan_fusion(const sv_gate* g, size_t n, int n_qubits, const sv_run_opts& o, std::vector<FusedGate>& fused,
                 std::vector<int32_t>& block_of, int max_ctrl);
@@ -277,11 +264,10 @@ BatchOut batch_run_impl(sv_state* const* states, const int* ns, const sv_gate* c
   std::vector<size_t> data_off(n_circ, 0);
   size_t data = 0, table_bytes = 0;
   uint64_t state_bytes = 0;
-  const int lds_n = batch_lds_max_n();
   for (size_t c = 0; c < n_circ; ++c) {
     const CircPlan& pl = plans[c];
     out.passes += pl.fused.size();
-    out.bytes += ((uint64_t)16 << ns[c]) * (ns[c] <= lds_n ? (pl.fused.empty() ? 0 : 1) : pl.fused.size());
+    out.bytes += ((uint64_t)16 << ns[c]) * pl.fused.size();
     if (pl.whole) {
       if (ns[c] > kBatchAloneQubits) throw DeviceError{hipErrorInvalidValue, "batch: a pass no tile takes"};
       alone.push_back(BCirc{(float2*)state_psi(states[c]), ns[c], (int)passes.size(), (int)pl.fused.size()});
@@ -404,7 +390,7 @@ extern "C" int sv_batch_run(sv_state* const* states, const sv_gate* const* circu
     if (ns[c] > 30) return fail(SV_EINVAL, "batched circuits are limited to 30 qubits");
     if (int rc = validate_gates(circuits[c], n_gates[c], ns[c])) return rc;
   }
-  // batched passes run on the VALU kernels; the precision field only selects FP32
+  // batched passes multiply in FP32, whatever the options say
   o.precision = SV_PREC_FP32_VALU;
   std::vector<hipEvent_t> waits;
   try {

@@ -31,8 +31,6 @@ int state_n(sv_state* s);
 hipStream_t state_stream(sv_state* s);
 bool state_poisoned(sv_state* s);
 void state_poison(sv_state* s);
-int batch_lds_max_n();
-void set_batch_lds_max_n(int n);
 
 namespace {
 
@@ -224,7 +222,7 @@ int sv_tune_save(const char* path) {
     std::lock_guard<std::mutex> lk(g_mu);
     std::ofstream f(path);
     if (!f) return fail(SV_EINVAL, std::string("cannot write ") + path);
-    f << "{\"format\": \"libsv-tune-1\", \"batch_lds_max_n\": " << batch_lds_max_n() << ", \"entries\": [";
+    f << "{\"format\": \"libsv-tune-1\", \"entries\": [";
     bool first = true;
     for (auto& kv : g_table) {
       f << (first ? "" : ", ") << "[" << std::get<0>(kv.first) << ", " << std::get<1>(kv.first) << ", "
@@ -267,12 +265,12 @@ int sv_tune_load(const char* path) {
       parsed[Key{p, k, q0, nlow}] = Choice{var, tb, ms};
       pos = close + 1;
     }
+    // a limit that files of earlier versions carry; nothing goes by it any more
     const size_t bl = text.find("\"batch_lds_max_n\"");
     if (bl != std::string::npos) {
       int v = 0;
       if (std::sscanf(text.c_str() + text.find(':', bl) + 1, "%d", &v) != 1 || v < 1 || v > 14)
         return fail(SV_EINVAL, "batch_lds_max_n out of range");
-      set_batch_lds_max_n(v);
     }
     {
       std::lock_guard<std::mutex> lk(g_mu);
