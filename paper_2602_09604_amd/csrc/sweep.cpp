@@ -27,10 +27,15 @@ uint32_t bit_mask(int b) {
 }
 }  // namespace
 
-// Tile size of an n-qubit state.
+// Tile size of an n-qubit state.  FP32: 2^12 amplitudes while a workgroup has at
+// most two tiles, 2^13 above, where fewer sweeps count for more (grid at greedy
+// k = 4 / grid unfused / quantum volume in blocks of 5, us with 2^12 and 2^13: 20
+// qubits 225, 293 / 396, 538 / 136, 202; 21: 377, 369 / 566, 662 / 220, 263; 22: 444,
+// 426 / 1002, 866 / 357, 367; 23: 491, 445 / 1694, 1480 / 612, 569; 25: 3500, 3255 /
+// 8429, 7197 / 2195, 2008).
 int sweep_tile_bits(int n, int precision) {
   if (split_precision(precision)) return std::min(n, 12);  // room for two 64 KiB matrices
-  return n <= 20 ? std::min(n, 12) : 13;
+  return n <= 21 ? std::min(n, 12) : 13;
 }
 
 // The FP32 passes of every size (the split precisions keep their own kernels
