@@ -316,7 +316,6 @@ __device__ __forceinline__ void sweep_tiles(float4* __restrict__ psi, const unsi
       switch (op.kind) {
         case 1: op_valu<T, NW, 1>(tile, op, data, wave, lane); break;
         case 2: op_valu<T, NW, 2>(tile, op, data, wave, lane); break;
-        case 3: op_mfma<T, NW, 3>(tile, op, mats, wave, lane); break;
         case 4: op_mfma<T, NW, 4>(tile, op, mats, wave, lane); break;
         default:  // kinds are set on the host
           if constexpr (PREC != SV_PREC_FP32_MFMA) {
@@ -324,7 +323,8 @@ __device__ __forceinline__ void sweep_tiles(float4* __restrict__ psi, const unsi
             else if (op.kind == kSweepSplit + 5) op_split<T, NW, 5, PREC>(tile, op, mats, wave, lane);
             else if (op.kind == kSweepSplit + 6) op_split<T, NW, 6, PREC>(tile, op, mats, wave, lane);
           }
-          if (op.kind == 5) op_mfma<T, NW, 5>(tile, op, mats, wave, lane);
+          if (op.kind == 3) op_mfma<T, NW, 3>(tile, op, mats, wave, lane);
+          else if (op.kind == 5) op_mfma<T, NW, 5>(tile, op, mats, wave, lane);
           else if (op.kind == 6) op_mfma<T, NW, 6>(tile, op, mats, wave, lane);
       }
       tile_sync();
