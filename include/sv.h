@@ -51,8 +51,9 @@ extern "C" {
  * ALUs for a pass launched by itself with k <= 4 (register passes with at most
  * four targets besides bit 0 multiply in the 3M form, three real products per
  * complex multiply-accumulate, with the matrix's ur + ui and ui - ur formed
- * in FP64), and on the FP32 matrix cores, in FP32_MFMA's 4M form, for k >= 5
- * and for the k >= 3 passes of a tile sweep.
+ * in FP64), and on the FP32 matrix cores, in FP32_MFMA's 4M form, for the
+ * k >= 3 passes of a tile sweep and for k >= 5 by itself (as a sweep of one
+ * pass; at k = 5 the vector ALUs on the largest states).
  * FP32_MFMA: passes with k >= 4 as a real GEMM in the 4M form
  * [Yr;Yi] = [[Ur,-Ui],[Ui,Ur]] [Xr;Xi] on FP32 matrix cores.
  * BF16X3 / FP16X3: the same GEMM with every operand split into hi + lo
@@ -78,9 +79,10 @@ extern "C" {
  * PHASE) with the cost-model network loaded by sv_cost_model_load and keeps
  * the cheapest, unless it has more passes than the fewest-pass candidate and
  * is predicted less than 5 % cheaper; with no model loaded it keeps the
- * candidate with the fewest passes (every pass moves the same bytes).  For
- * states of 28 qubits and more at BF16X3, FP16X3 or FP32_MFMA, LEARNED also
- * lets a block take diagonal gates that reach up to 3 qubits outside its
+ * candidate with the fewest passes.  Both price passes one by one: that
+ * several may share one trip through memory (tile sweeps) is not part of it.
+ * For states of 28 qubits and more at BF16X3, FP16X3 or FP32_MFMA, LEARNED
+ * also lets a block take diagonal gates that reach up to 3 qubits outside its
  * targets (at bit 4 or above) as control bits: such a block is one gate per
  * control value on the same targets, and sv_apply_circuit runs all of them
  * as one matrix-core launch when the block has k >= 4 targets.  PHASE is
@@ -147,7 +149,10 @@ typedef struct {
   int32_t variant;    /* SV_VARIANT_* (AUTO unless a test forces one) */
   int32_t timing;     /* 1: bracket every pass with HIP events on the handle's
                          stream and report per-variant device time in stats
-                         (needs stats; passes are then launched without a graph) */
+                         (needs stats).  Every pass is then a launch of its own,
+                         without a graph and without tile sweeps: the figures are
+                         those of the passes, not of the call without timing, and
+                         amplitudes may round differently */
 } sv_run_opts;
 
 typedef struct {
@@ -182,8 +187,9 @@ typedef struct {
  * |0...0> into it (asynchronously on `hip_stream`, a hipStream_t or NULL for
  * the default stream).  dev_buf must hold at least 8 * 2^n bytes and stay
  * valid until sv_free; it is never freed by the library.  1 <= n <= 40.
- * The library allocates only the handle and a small device arena for gate
- * matrices and reduction partials.  Errors: SV_EINVAL (n, dtype, null),
+ * The library allocates only the handle and a device arena for gate matrices
+ * and reduction partials, which grows with the largest call; state reads and
+ * batches add the scratch their entries name.  Errors: SV_EINVAL (n, dtype, null),
  * SV_ENOMEM (buf_bytes < 8 * 2^n or arena allocation). */
 int sv_alloc(int n_qubits, int dtype, void* dev_buf, size_t buf_bytes, void* hip_stream,
              sv_state** out);
@@ -301,6 +307,8 @@ int sv_marginal_probs(sv_state* s, int n_meas, const int32_t* qubits, double* ou
  * uniforms[j] * sum(p) (FP64 prefix sums; a value past the end, from
  * rounding, takes the last index with p_i > 0).  The caller draws the
  * uniforms, so the result is reproducible.  The state is not changed.
+ * Device scratch stays with the handle: 72 bytes per 4096 amplitudes (19 MB at
+ * 30 qubits, 302 MB from 34) and 16 per shot of a call, up to 2^20 shots.
  * Synchronises.  SV_EINVAL: a uniform outside [0, 1), NULL arrays, or a
  * zero state. */
 int sv_sample(sv_state* s, size_t n_shots, const double* uniforms, uint64_t* out);

@@ -111,8 +111,9 @@ double cost_model_predict_log(int k, const int* qubits, int n, int precision) {
 
 bool fuse_learned(const sv_gate* g, size_t n, int n_qubits, int max_k, int precision, std::vector<FusedGate>& out,
                   std::vector<int32_t>& block_of, int max_ctrl) {
-  // Without a model every pass costs the same (it moves the same bytes): the
-  // search then keeps the candidate with the fewest passes.
+  // Without a model every pass costs the same (by itself it moves the same
+  // bytes; that passes may share a tile sweep is not priced): the search then
+  // keeps the candidate with the fewest passes.
   const bool model = cost_model_ready();
   std::unordered_map<uint64_t, double> cache;
   const double amps = std::ldexp(1.0, n_qubits);
