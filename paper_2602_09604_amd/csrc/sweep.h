@@ -14,15 +14,16 @@ constexpr size_t kSweepLds = 163840;  // what a workgroup may take: a CU's 160 K
 // LDS for the matrices of a sweep of an n-qubit state: so that two workgroups
 // share a CU's 160 KiB (a sweep of one larger matrix takes more and runs
 // alone), or all of it where the state is a single tile and, for split
-// matrices (64 KiB at k = 6), up to 21 qubits, where a workgroup has one or two
-// tiles, and from 25, where the sweep saved is worth more than the second
-// workgroup (16 FP16X3 passes with k = 6, all in pairs / a quantum volume in blocks
-// of 6, us with all of the LDS and half of it: 20 qubits 122, 185 / 150, 190; 21: 237,
-// 276 / 242, 273; 22: 322, 278 / 372, 355; 23: 516, 445 / 558, 536; 24: 862, 854 / 1066,
-// 1060; 25: 1546, 1527 / 1941, 1991; 26: 2795, 3123 / 4328, 4420).
+// matrices (64 KiB at k = 6), up to 20 qubits, where a CU has one tile anyway,
+// and from 25, where the sweep saved is worth more than the second workgroup
+// (16 FP16X3 passes with k = 6, all in pairs / a quantum volume in blocks of 6, us
+// with all of the LDS and half of it: 20 qubits 122, 185 / 150, 190; 22: 322, 278 /
+// 372, 355; 23: 516, 445 / 558, 536; 24: 862, 854 / 1066, 1060; 25: 1546, 1527 / 1941,
+// 1991; 26: 2795, 3123 / 4328, 4420; at 21, 237, 276 / 242, 273, but there it would
+// change the order of passes, and with it the rounding of a BF16X3 circuit by 2.5e-5).
 inline size_t sweep_mat_room(int n, int T, int precision) {
   const bool split = precision == SV_PREC_BF16X3 || precision == SV_PREC_FP16X3;
-  const bool all = T == n || (split && (n <= 21 || n >= 25));
+  const bool all = T == n || (split && (n <= 20 || n >= 25));
   return (all ? kSweepLds : kSweepLds / 2) - ((size_t)8 << T);
 }
 constexpr int kSweepLow = 4;       // low state bits in every tile: whole 128-byte lines
