@@ -52,7 +52,12 @@ __device__ __forceinline__ float2& amp(unsigned char* t, uint32_t byte) { return
 // A K-qubit pass on the matrix cores.  A wave takes UPW whole units, or, when
 // the tile has fewer units than the workgroup waves, WPU waves share a unit
 // and split its output rows (all of them read the unit before any writes it).
-template <int T, int NW, int K>
+// PAIRS (K = 3 in BF16X3 sweeps): each instruction adds two products, amplitudes
+// a and a + 4, instead of four, the others being 0 * 0: the order in which the
+// sums were formed when these passes ran as K = 4.  A last bit that falls
+// differently here moves the 16-bit splits of the passes that follow by up to
+// 1.7e-5 of the result.
+template <int T, int NW, int K, bool PAIRS = false>
 __device__ __forceinline__ void op_mfma(unsigned char* tile, const SweepOp& op, const unsigned char* mats, int wave,
                                         int lane) {
   if constexpr (T >= K + 4) {
@@ -104,12 +109,17 @@ __device__ __forceinline__ void op_mfma(unsigned char* tile, const SweepOp& op, 
           a[q][3] = im ? f.z : -f.w;
         }
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
+        for (int half = 0; half < (PAIRS ? 2 : 1); ++half) {
+          const bool in = !PAIRS || ((lane >> 4) & 1) == half;
 #pragma unroll
-          for (int q = 0; q < TB; ++q)
+          for (int s = 0; s < 4; ++s)
 #pragma unroll
-            for (int u = 0; u < UPW; ++u)
-              acc[q][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][s], b[u][4 * i2 + s], acc[q][u], 0, 0, 0);
+            for (int q = 0; q < TB; ++q)
+#pragma unroll
+              for (int u = 0; u < UPW; ++u)
+                acc[q][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? a[q][s] : 0.f, in ? b[u][4 * i2 + s] : 0.f,
+                                                                 acc[q][u], 0, 0, 0);
+        }
       }
 #pragma unroll
       for (int q = 0; q < TB; ++q)
@@ -323,7 +333,7 @@ __device__ __forceinline__ void sweep_tiles(float4* __restrict__ psi, const unsi
             else if (op.kind == kSweepSplit + 5) op_split<T, NW, 5, PREC>(tile, op, mats, wave, lane);
             else if (op.kind == kSweepSplit + 6) op_split<T, NW, 6, PREC>(tile, op, mats, wave, lane);
           }
-          if (op.kind == 3) op_mfma<T, NW, 3>(tile, op, mats, wave, lane);
+          if (op.kind == 3) op_mfma<T, NW, 3, PREC == SV_PREC_BF16X3>(tile, op, mats, wave, lane);
           else if (op.kind == 5) op_mfma<T, NW, 5>(tile, op, mats, wave, lane);
           else if (op.kind == 6) op_mfma<T, NW, 6>(tile, op, mats, wave, lane);
       }

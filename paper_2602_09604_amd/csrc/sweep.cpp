@@ -19,6 +19,14 @@ size_t op_mat_bytes(int kind) {  // complex64, or the real 2^(K+1) square matrix
 }
 size_t lds_mat_bytes(int kind) { return kind > 2 ? op_mat_bytes(kind) : 0; }
 
+// What a matrix counts for when the sweeps of a circuit are planned.  BF16X3: a k
+// = 3 one as a k = 4 one, so that the same passes share a sweep as when it was
+// padded to that; another order of passes moves a BF16X3 result by as much as its
+// error (2 to 3e-5 after a few dozen passes).
+size_t planned_mat_bytes(int kind, int precision) {
+  return lds_mat_bytes(kind == 3 && precision == SV_PREC_BF16X3 ? 4 : kind);
+}
+
 // byte-address mask of tile bit b (the swizzle of k_sweep.hip on one bit)
 uint32_t bit_mask(int b) {
   if (b == 0) return 8;
@@ -95,17 +103,18 @@ void plan_sweeps(const std::vector<SweepItem>& items, int n, int T, size_t mat_r
       if (split_precision(precision)) sw.precision = precision;
       sw.low = low;
       sw.bits = low_mask | items[s].mask;
-      size_t mat = lds_mat_bytes(items[s].kind);
+      size_t mat = lds_mat_bytes(items[s].kind), planned = planned_mat_bytes(items[s].kind, precision);
       sw.data_bytes = sizeof(SweepOp) + op_mat_bytes(items[s].kind);
       uint64_t blocked = 0;
       for (size_t h = s + 1; h < items.size(); ++h) {
         if (used[h]) continue;
         const uint64_t m = items[h].mask;
-        const size_t mb = lds_mat_bytes(items[h].kind);
+        const size_t mb = planned_mat_bytes(items[h].kind, precision);
         if (items[h].kind && (m & blocked) == 0 && __builtin_popcountll(sw.bits | m) <= T &&
-            mat + mb <= mat_room) {
+            planned + mb <= mat_room) {
           sw.bits |= m;
-          mat += mb;
+          planned += mb;
+          mat += lds_mat_bytes(items[h].kind);
           sw.data_bytes += sizeof(SweepOp) + op_mat_bytes(items[h].kind);
           sw.members.push_back((int)h);
           used[h] = 1;
